@@ -84,6 +84,7 @@ struct BoxHost {
     size_t off_f[2] = {0, 0}, off_stamp[2] = {0, 0}, off_F = 0, off_u = 0, off_ufull = 0;
     size_t off_mask[2] = {0, 0};
     int nzw = 0;  // 64-bit mask words per column (boxes with tau_in)
+    int obs_begin = 0, obs_end = 0;  // row groups of the observables
 };
 
 struct Plan {
@@ -93,7 +94,7 @@ struct Plan {
     int real = 4;  // bytes of the compute type
     std::vector<BoxHost> boxes;
     std::vector<DropHost> drops;
-    int Ntot = 0, nblk = 0, Ttot = 0, n_chunks = 0, total_tiles = 0;
+    int Ntot = 0, nblk = 0, Ttot = 0, n_chunks = 0, total_tiles = 0, n_obs_groups = 0;
     size_t max_rows = 0;  // capacity of the bulk row-group table
     bool any_kvol = false;
     // workspace offsets
@@ -101,8 +102,8 @@ struct Plan {
            off_trec = 0, off_tile_list = 0, off_tile_count = 0, off_part = 0, off_breg = 0,
            off_base = 0, off_s0 = 0, off_bbox = 0, off_blk_drop = 0, off_tri = 0,
            off_csr_off = 0, off_csr_ent = 0, off_chunks = 0, off_tri_part = 0, off_rows = 0,
-           off_tchunk = 0, off_tcand = 0, off_tncand = 0, off_scan = 0, off_ctr = 0, off_step_epoch = 0, off_status = 0, off_obs_part = 0,
-           off_obs_out = 0,
+           off_tchunk = 0, off_tcand = 0, off_tncand = 0, off_scan = 0, off_ctr = 0, off_step_epoch = 0, off_status = 0, off_obs_groups = 0,
+           off_obs_part = 0, off_obs_part1 = 0, off_obs_part2 = 0,
            off_uout = 0, total = 0;
     // the same per-step arrays inside the fixed scratch (iblb_step_static)
     size_t st_trec = 0, st_tri_part = 0, st_bbox = 0, st_breg = 0, st_part = 0, st_tile_list = 0,
@@ -255,6 +256,10 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
         H.n_tiles = H.tnx * H.tny * H.tnz;
         H.tile_base = p.total_tiles;
         p.total_tiles += (int)round_up((size_t)H.n_tiles, TILE_CELLS);
+        const int64_t rows = (int64_t)B.ny * B.nz;
+        H.obs_begin = p.n_obs_groups;
+        p.n_obs_groups += obs_groups_of(rows, rows * B.nx);
+        H.obs_end = p.n_obs_groups;
         // row segments of at least 64 cells, plus the empty row groups that
         // fill the last group of eight
         p.max_rows += ((size_t)B.ny * B.nz + 7) * ((B.nx + 63) / 64);
@@ -391,8 +396,10 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_ctr = take(4);
     p.off_step_epoch = take(2 * 4);
     p.off_status = take(4);
-    p.off_obs_part = take(2 * (size_t)OBS_GROUPS * 8);
-    p.off_obs_out = take(((size_t)p.drops.size() * OBS_DROP + p.boxes.size() * OBS_BOX) * 8);
+    p.off_obs_groups = take(sizeof(ObsGroup) * (size_t)p.n_obs_groups);
+    p.off_obs_part = take(2 * (size_t)p.n_obs_groups * 8);
+    p.off_obs_part1 = take((size_t)OBS_PASS1 * p.n_chunks * 8);
+    p.off_obs_part2 = take((size_t)OBS_PASS2 * p.n_chunks * 8);
     p.off_uout = take(3 * N * 8);
     p.total = round_up(o, ALIGN);
     o = 0;
@@ -438,8 +445,7 @@ struct iblb_ctx {
     hipEvent_t ev_chain = nullptr, ev_bulk = nullptr;  // joins inside a run of steps
     bool unstable = false;
     std::string err = "no error";
-    double *host_obs = nullptr;
-    uint32_t *host_status = nullptr;
+    double *host_obs = nullptr;  // pinned: the observables' kernels write it
     std::vector<char> init_qh, init_ql;  // initial node positions, kept during init only
 };
 
@@ -1030,14 +1036,16 @@ static iblb_status init_device(iblb_ctx *c) {
     P.ctr = (int32_t *)at(p.off_ctr);
     P.step_epoch = (int32_t *)at(p.off_step_epoch);
     P.status = (uint32_t *)at(p.off_status);
+    P.obs_groups = (ObsGroup *)at(p.off_obs_groups);
     P.obs_part = (double *)at(p.off_obs_part);
-    P.obs_out = (double *)at(p.off_obs_out);
+    P.obs_part1 = (double *)at(p.off_obs_part1);
+    P.obs_part2 = (double *)at(p.off_obs_part2);
     P.Ntot = p.Ntot;
     P.nblk = p.nblk;
     P.Ttot = p.Ttot;
     P.n_chunks = p.n_chunks;
     P.total_tiles = p.total_tiles;
-    P.obs_groups = OBS_GROUPS;
+    P.n_obs_groups = p.n_obs_groups;
     {
         int dev = 0, cus = 0;
         HIPCHK(c, hipGetDevice(&dev));
@@ -1049,6 +1057,7 @@ static iblb_status init_device(iblb_ctx *c) {
     // host tables
     std::vector<BoxDev> bd(p.boxes.size());
     std::vector<int32_t> tchunk(p.total_tiles / TILE_CELLS, 0);
+    std::vector<ObsGroup> og(p.n_obs_groups);
     for (size_t b = 0; b < p.boxes.size(); ++b) {
         const BoxHost &H = p.boxes[b];
         BoxDev &D = bd[b];
@@ -1087,6 +1096,11 @@ static iblb_status init_device(iblb_ctx *c) {
         D.uw[1] = H.b.wall_lo[1];
         D.uw[2] = H.b.wall_hi[0];
         D.uw[3] = H.b.wall_hi[1];
+        D.obs_begin = H.obs_begin;
+        D.obs_end = H.obs_end;
+        const int64_t rows = (int64_t)H.b.ny * H.b.nz, ng = H.obs_end - H.obs_begin;
+        for (int64_t k = 0; k < ng; ++k)
+            og[H.obs_begin + k] = {(int32_t)b, (int32_t)(rows * k / ng), (int32_t)(rows * (k + 1) / ng), 0};
         D.moving = (D.uw[0] != 0.0 || D.uw[1] != 0.0 || D.uw[2] != 0.0 || D.uw[3] != 0.0) ? 1 : 0;
         if (D.moving) P.moving = 1;
         if (D.contrast) {
@@ -1173,6 +1187,7 @@ static iblb_status init_device(iblb_ctx *c) {
     HIPCHK(c, hipMemcpyAsync(P.csr_ent, csr_ent.data(), 3 * (size_t)p.Ttot * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.blk_drop, blk_drop.data(), (size_t)p.nblk * 8, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.chunks, chunks.data(), (size_t)p.n_chunks * sizeof(TriChunk), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(P.obs_groups, og.data(), og.size() * sizeof(ObsGroup), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.tchunk_box, tchunk.data(), tchunk.size() * 4, hipMemcpyHostToDevice, c->stream));
     // fluid at rest: all deviations zero; no tile stamped; band zeroed
     for (auto &H : p.boxes) {
@@ -1233,8 +1248,7 @@ static iblb_status init_device(iblb_ctx *c) {
     if (st == IBLB_OK) {
         if (hipHostMalloc((void **)&c->host_obs,
                           ((size_t)P.n_drops * OBS_DROP + (size_t)P.n_boxes * OBS_BOX) * 8 + 64,
-                          hipHostMallocDefault) != hipSuccess ||
-            hipHostMalloc((void **)&c->host_status, 64, hipHostMallocDefault) != hipSuccess)
+                          hipHostMallocDefault) != hipSuccess)
             st = set_err(c, IBLB_E_DEVICE, "pinned host buffer allocation failed");
     }
     return st;
@@ -1404,13 +1418,10 @@ iblb_status iblb_observables(iblb_ctx *c, iblb_obs *per_drop, int32_t n_drops, i
         iblb_status st = flush(c);
         if (st != IBLB_OK) return st;
     }
-    HIPCHK(c, launch_box_obs(c->P, c->plan.storage, c->parity, (float)(1.0 / c->plan.scale), c->stream));
-    HIPCHK(c, launch_drop_obs(c->P, is_f64(c), c->stream));
     const size_t nobs = (size_t)c->P.n_drops * OBS_DROP + (size_t)c->P.n_boxes * OBS_BOX;
-    HIPCHK(c, hipMemcpyAsync(c->host_obs, c->P.obs_out, nobs * 8, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->host_status, c->P.status, 4, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, launch_obs(c->P, c->plan.storage, c->parity, (float)(1.0 / c->plan.scale), c->host_obs, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    const uint32_t bits = *c->host_status;
+    const uint32_t bits = (uint32_t)c->host_obs[nobs];
     if (per_drop)
         for (int d = 0; d < c->P.n_drops; ++d) {
             const double *o = c->host_obs + (size_t)d * OBS_DROP;
@@ -2095,7 +2106,6 @@ iblb_status iblb_destroy(iblb_ctx *c) {
     if (c->ev_chain) (void)hipEventDestroy(c->ev_chain);
     if (c->ev_bulk) (void)hipEventDestroy(c->ev_bulk);
     if (c->host_obs) (void)hipHostFree(c->host_obs);
-    if (c->host_status) (void)hipHostFree(c->host_status);
     delete c;
     return IBLB_OK;
 }

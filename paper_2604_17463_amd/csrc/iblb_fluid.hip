@@ -2,8 +2,8 @@
 // pull-stream / moments / BGK-Guo collision with the body force only, over
 // every cell outside this step's stamped band tiles; the band kernel, which
 // gathers the spread interface force for each stamped tile and does the
-// collision of its 64 cells with it; and the per-box observables.  The two
-// step kernels write disjoint cells and run side by side.
+// collision of its 64 cells with it.  The two write disjoint cells and run
+// side by side.
 #include "iblb_device.h"
 
 namespace iblb {
@@ -455,93 +455,6 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-// ------------------------------------------------------------ observables
-__device__ __forceinline__ double block_sum256(double v, double *sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
-}
-__device__ __forceinline__ double block_max256(double v, double *sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + s]);
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
-}
-
-// Mass and largest bare velocity of one box's current populations: fixed
-// partition of the rows over OBS_GROUPS workgroups, then a fixed-order
-// final sum.
-template <int ST>
-__global__ void __launch_bounds__(256) k_box_obs(DevPtrs P, int box, int parity, float inv) {
-    using S = Stor<ST>;
-    using R = typename S::R;
-    __shared__ double sh[256];
-    const BoxDev &B = P.boxes[box];
-    const int rows = B.ny * B.nz;
-    const int r0 = (int)((int64_t)rows * blockIdx.x / gridDim.x);
-    const int r1 = (int)((int64_t)rows * (blockIdx.x + 1) / gridDim.x);
-    const IBLB_GLOBAL char *src = (const IBLB_GLOBAL char *)B.f[parity];
-    const uint64_t pb = (uint64_t)B.plane * sizeof(typename S::T);
-    double m = 0.0, umax = 0.0;
-    for (int r = r0; r < r1; ++r) {
-        const int z = r / B.ny, y = r - z * B.ny;
-        const RowAddr ra = row_addr(y, z, B.ny, B.nz, B.sx, B.zbc == 1, sizeof(typename S::T));
-        for (int x = threadIdx.x; x < B.nx; x += 256) {
-            R g[Q];
-            pull<ST>(src, pb, ra, x, B.nx, inv, g);
-            if (B.moving && (ra.wlo || ra.whi)) {  // g holds unscaled deviations
-                R kw[4];
-#pragma unroll
-                for (int a = 0; a < 4; ++a) kw[a] = (R)(6.0 * B.rho0 * B.uw[a]);
-                wall_shift<R>(g, ra.wlo, ra.whi, kw);
-            }
-            double dr = 0, jx = 0, jy = 0, jz = 0;
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                dr += (double)g[i];
-                jx += cx_of(i) * (double)g[i];
-                jy += cy_of(i) * (double)g[i];
-                jz += cz_of(i) * (double)g[i];
-            }
-            m += dr;
-            umax = fmax(umax, sqrt(jx * jx + jy * jy + jz * jz) / (B.rho0 + dr));
-        }
-    }
-    m = block_sum256(m, sh);
-    umax = block_max256(umax, sh);
-    if (threadIdx.x == 0) {
-        P.obs_part[2 * blockIdx.x] = m;
-        P.obs_part[2 * blockIdx.x + 1] = umax;
-    }
-}
-
-__global__ void __launch_bounds__(256) k_box_obs_final(DevPtrs P, int box, int groups) {
-    __shared__ double sh[256];
-    double m = 0.0, umax = 0.0;
-    for (int k = threadIdx.x; k < groups; k += 256) {
-        m += P.obs_part[2 * k];
-        umax = fmax(umax, P.obs_part[2 * k + 1]);
-    }
-    m = block_sum256(m, sh);
-    umax = block_max256(umax, sh);
-    if (threadIdx.x == 0) {
-        double *o = P.obs_out + P.n_drops * OBS_DROP + box * OBS_BOX;
-        o[0] = P.boxes[box].cells_rho0 + m;
-        o[1] = umax;
-    }
-}
-
 // ---------------------------------------------------------------- launchers
 template <int ST, bool UROW, bool NT, bool SKIP, bool PADW>
 static void launch_bulk_p(const DevPtrs &P, int parity, int full_u, float scale, float inv, const Launch &L,
@@ -641,20 +554,6 @@ hipError_t launch_band(const DevPtrs &P, int storage, int parity, int full_u, fl
         launch_band_t<0, false>(P, parity, full_u, scale, 0, s);
     } else {
         launch_band_t<1, false>(P, parity, full_u, scale, 0, s);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_box_obs(const DevPtrs &P, int storage, int parity, float inv, hipStream_t s) {
-    for (int b = 0; b < P.n_boxes; ++b) {
-        const dim3 grid(OBS_GROUPS), block(256);
-        switch (storage) {
-        case 0: hipLaunchKernelGGL(k_box_obs<0>, grid, block, 0, s, P, b, parity, inv); break;
-        case 1: hipLaunchKernelGGL(k_box_obs<1>, grid, block, 0, s, P, b, parity, inv); break;
-        case 2: hipLaunchKernelGGL(k_box_obs<2>, grid, block, 0, s, P, b, parity, inv); break;
-        default: hipLaunchKernelGGL(k_box_obs<3>, grid, block, 0, s, P, b, parity, inv); break;
-        }
-        hipLaunchKernelGGL(k_box_obs_final, dim3(1), dim3(256), 0, s, P, b, OBS_GROUPS);
     }
     return hipGetLastError();
 }

@@ -148,7 +148,9 @@ struct BoxDev {
     int32_t contrast, nzw;      // tau_in set; 64-bit words per column (ceil(nz/64))
     uint64_t *mask[2];          // [nzw][ny][nx] inside bits, one set per step parity
     double uw[4];               // moving walls: u_x, u_y at z = 0, then at z = nz
-    int32_t moving, pad;        // some wall velocity is nonzero
+    int32_t moving;             // some wall velocity is nonzero
+    int32_t obs_begin, obs_end; // the box's row groups of the observables
+    int32_t pad;
 };
 
 struct DropDev {
@@ -163,6 +165,11 @@ struct RowGroup {
     int32_t box, r0, r1;        // rows r = z*ny + y in [r0, r1)
     int32_t x0, x1;             // cells x0 <= x < x1 of those rows (x1 > nx: the padding too)
     int32_t pad[3];
+};
+
+// Rows r0 <= r < r1 of a box that one workgroup of the observables takes.
+struct ObsGroup {
+    int32_t box, r0, r1, pad;
 };
 
 struct TriChunk {
@@ -199,10 +206,12 @@ struct DevPtrs {
     int32_t *ctr;               // step epoch
     int32_t *step_epoch;        // [2] epoch of the last node pass, by buffer parity
     uint32_t *status;
-    double *obs_part;           // observables scratch
-    double *obs_out;            // per droplet [12], per box [2]
+    ObsGroup *obs_groups;       // row groups of the observables, box by box
+    double *obs_part;           // [n_obs_groups][2] mass, max_u
+    double *obs_part1;          // [n_chunks][OBS_PASS1], [n_chunks][OBS_PASS2]: sums per
+    double *obs_part2;          // triangle chunk of the observables' two passes
     int32_t Ntot, nblk, Ttot, n_chunks;
-    int32_t n_rowgroups, total_tiles, obs_groups, n_cus;  // n_cus: compute units of the device
+    int32_t n_rowgroups, total_tiles, n_obs_groups, n_cus;  // n_cus: compute units of the device
     int32_t contrast;           // some box has tau_in set
     int32_t moving;             // some box has a moving wall
     int32_t mask_words;         // largest nzw*ny*nx over those boxes
@@ -233,14 +242,25 @@ hipError_t launch_epoch(const DevPtrs &P, hipStream_t s);
 hipError_t launch_inside(const DevPtrs &P, bool f64, int slot, hipStream_t s);
 hipError_t launch_mask_clear(const DevPtrs &P, int slot, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
-hipError_t launch_box_obs(const DevPtrs &P, int storage, int parity, float inv_scale,
-                          hipStream_t s);
-hipError_t launch_drop_obs(const DevPtrs &P, bool f64, hipStream_t s);
+// Observables of the current state into `out` (pinned host memory): per
+// droplet OBS_DROP values, per box OBS_BOX, then the status word.
+hipError_t launch_obs(const DevPtrs &P, int storage, int parity, float inv_scale, double *out, hipStream_t s);
 
 // vol, area, zmin, zmax, cx, cy, cz, rsum, count, then the volume moments
 // about the node mean m: V, int (x-m), int (x-m)(x-m)^T (xx yy zz xy xz yz)
 constexpr int OBS_DROP = 20;
 constexpr int OBS_BOX = 2;   // mass, max_u
-constexpr int OBS_GROUPS = 512;
+constexpr int OBS_PASS1 = 10, OBS_PASS2 = 12;
+// Row groups (workgroups) of a box in the observables: one per 512 cells up
+// to 256 groups, so that a small box is not a few waves walking many rows in
+// turn (16 groups of 4,096 cells took 34 us on 45x37x41), then one per 2,048
+// cells up to 2,048 groups (512 groups left two-byte storage at 8 waves per
+// CU: 2.4 TB/s on 256x256x128 in BF16).  By the box alone, so that its sums
+// do not depend on the other boxes of the context.
+inline int obs_groups_of(int64_t rows, int64_t cells) {
+    const int64_t few = cells / 512 < 256 ? cells / 512 : 256, many = cells / 2048 < 2048 ? cells / 2048 : 2048;
+    const int64_t n = few > many ? few : many;
+    return (int)(n < 1 ? 1 : (n < rows ? n : rows));
+}
 
 }  // namespace iblb

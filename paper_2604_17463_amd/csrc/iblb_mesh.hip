@@ -1,9 +1,9 @@
 // Mesh kernels of the IBLB wetting step (gfx950): per-triangle records,
 // the node pass (interface forces, Peskin weights, tile stamps and the
 // block-partial spread), the stamped-tile list, interpolation with forward
-// Euler advection, the inside bits of the viscosity contrast, and the
-// per-droplet observables.
-#include "iblb_device.h"
+// Euler advection, and the inside bits of the viscosity contrast; and the
+// observables (iblb_obs.h).
+#include "iblb_obs.h"
 
 namespace iblb {
 
@@ -605,136 +605,6 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t n) {
         p[i] = v;
 }
 
-// ------------------------------------------------------------ observables
-__device__ __forceinline__ double block_sum256(double v, double *sh) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
-}
-__device__ __forceinline__ double block_minmax256(double v, double *sh, bool mx) {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            sh[threadIdx.x] = mx ? fmax(sh[threadIdx.x], sh[threadIdx.x + s])
-                                 : fmin(sh[threadIdx.x], sh[threadIdx.x + s]);
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
-}
-
-// Per droplet (one workgroup): z range, FP64 area, volume and area-weighted
-// centroid, then the edge crossings of z = z_min + xi, and the moments of
-// the enclosed volume about the node mean m (for the deformation index):
-// over the tetrahedron (m, a, b, c) of each triangle, with p the corners
-// relative to m, s = p_a + p_b + p_c and v = p_a . (p_b x p_c) / 6,
-//   int dV = v,  int x dV = v s / 4,  int x x^T dV = v (sum p p^T + s s^T) / 20.
-template <typename R>
-__global__ void __launch_bounds__(256) k_drop_obs(DevPtrs P) {
-    __shared__ double sh[256];
-    const DropDev &D = P.drops[blockIdx.x];
-    const R *qh = (const R *)P.qh, *ql = (const R *)P.ql;
-    const int N = P.Ntot;
-    auto pos = [&](int j, int a) { return (double)qh[a * N + j] + (double)ql[a * N + j]; };
-    double zmin = DBL_MAX, zmax = -DBL_MAX;
-    for (int k = threadIdx.x; k < D.n_nodes; k += 256) {
-        const double z = pos(D.node_off + k, 2);
-        zmin = fmin(zmin, z);
-        zmax = fmax(zmax, z);
-    }
-    zmin = block_minmax256(zmin, sh, false);
-    zmax = block_minmax256(zmax, sh, true);
-    double mean[3];
-    for (int a = 0; a < 3; ++a) {
-        double s = 0;
-        for (int k = threadIdx.x; k < D.n_nodes; k += 256) s += pos(D.node_off + k, a);
-        mean[a] = block_sum256(s, sh) / (double)max(D.n_nodes, 1);
-    }
-    double mom[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    double vol = 0, area = 0, c0 = 0, c1 = 0, c2 = 0;
-    for (int t = D.tri_off + threadIdx.x; t < D.tri_off + D.n_tris; t += 256) {
-        double p[3][3];
-        for (int c = 0; c < 3; ++c)
-            for (int a = 0; a < 3; ++a) p[c][a] = pos(P.tri[3 * t + c], a) - D.ref[a];
-        const double bc0 = p[1][1] * p[2][2] - p[1][2] * p[2][1];
-        const double bc1 = p[1][2] * p[2][0] - p[1][0] * p[2][2];
-        const double bc2 = p[1][0] * p[2][1] - p[1][1] * p[2][0];
-        vol += (p[0][0] * bc0 + p[0][1] * bc1 + p[0][2] * bc2) / 6.0;
-        double e1[3], e2[3];
-        for (int a = 0; a < 3; ++a) {
-            e1[a] = p[1][a] - p[0][a];
-            e2[a] = p[2][a] - p[0][a];
-        }
-        const double n0 = e1[1] * e2[2] - e1[2] * e2[1];
-        const double n1 = e1[2] * e2[0] - e1[0] * e2[2];
-        const double n2 = e1[0] * e2[1] - e1[1] * e2[0];
-        const double At = 0.5 * sqrt(n0 * n0 + n1 * n1 + n2 * n2);
-        area += At;
-        c0 += At * (p[0][0] + p[1][0] + p[2][0]) / 3.0;
-        c1 += At * (p[0][1] + p[1][1] + p[2][1]) / 3.0;
-        c2 += At * (p[0][2] + p[1][2] + p[2][2]) / 3.0;
-        double r[3][3];
-        for (int c = 0; c < 3; ++c)
-            for (int a = 0; a < 3; ++a) r[c][a] = pos(P.tri[3 * t + c], a) - mean[a];
-        const double v = (r[0][0] * (r[1][1] * r[2][2] - r[1][2] * r[2][1]) +
-                          r[0][1] * (r[1][2] * r[2][0] - r[1][0] * r[2][2]) +
-                          r[0][2] * (r[1][0] * r[2][1] - r[1][1] * r[2][0])) / 6.0;
-        const double s[3] = {r[0][0] + r[1][0] + r[2][0], r[0][1] + r[1][1] + r[2][1],
-                             r[0][2] + r[1][2] + r[2][2]};
-        mom[0] += v;
-        for (int a = 0; a < 3; ++a) mom[1 + a] += v * s[a] / 4.0;
-        constexpr int I[6] = {0, 1, 2, 0, 0, 1}, J[6] = {0, 1, 2, 1, 2, 2};
-#pragma unroll
-        for (int e = 0; e < 6; ++e)
-            mom[4 + e] += v * (r[0][I[e]] * r[0][J[e]] + r[1][I[e]] * r[1][J[e]] + r[2][I[e]] * r[2][J[e]] +
-                               s[I[e]] * s[J[e]]) / 20.0;
-    }
-    for (int e = 0; e < 10; ++e) mom[e] = block_sum256(mom[e], sh);
-    vol = block_sum256(vol, sh);
-    area = block_sum256(area, sh);
-    c0 = block_sum256(c0, sh) / area + D.ref[0];
-    c1 = block_sum256(c1, sh) / area + D.ref[1];
-    c2 = block_sum256(c2, sh) / area + D.ref[2];
-    const double zc = zmin + D.xi;
-    double rs = 0, cnt = 0;
-    for (int t = D.tri_off + threadIdx.x; t < D.tri_off + D.n_tris; t += 256) {
-        for (int c = 0; c < 3; ++c) {
-            const int a = P.tri[3 * t + c], b = P.tri[3 * t + (c + 1) % 3];
-            if (a > b) continue;
-            const double za = pos(a, 2), zb = pos(b, 2);
-            if ((za < zc) == (zb < zc)) continue;
-            const double s = (zc - za) / (zb - za);
-            const double px = pos(a, 0) + s * (pos(b, 0) - pos(a, 0)) - c0;
-            const double py = pos(a, 1) + s * (pos(b, 1) - pos(a, 1)) - c1;
-            rs += sqrt(px * px + py * py);
-            cnt += 1.0;
-        }
-    }
-    rs = block_sum256(rs, sh);
-    cnt = block_sum256(cnt, sh);
-    if (threadIdx.x == 0) {
-        double *o = P.obs_out + blockIdx.x * OBS_DROP;
-        o[0] = vol;
-        o[1] = area;
-        o[2] = zmin;
-        o[3] = zmax;
-        o[4] = c0;
-        o[5] = c1;
-        o[6] = c2;
-        o[7] = rs;
-        o[8] = cnt;
-        for (int e = 0; e < 10; ++e) o[9 + e] = mom[e];
-    }
-}
-
 // ---------------------------------------------------------------- launchers
 hipError_t launch_tri(const DevPtrs &P, bool f64, hipStream_t s) {
     if (P.n_chunks == 0) return hipSuccess;
@@ -918,13 +788,6 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t g = (n + 255) / 256;
     hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)(g < 4096 ? g : 4096)), dim3(256), 0, s, p, v, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_drop_obs(const DevPtrs &P, bool f64, hipStream_t s) {
-    if (P.n_drops == 0) return hipSuccess;
-    if (f64) hipLaunchKernelGGL(k_drop_obs<double>, dim3(P.n_drops), dim3(256), 0, s, P);
-    else hipLaunchKernelGGL(k_drop_obs<float>, dim3(P.n_drops), dim3(256), 0, s, P);
     return hipGetLastError();
 }
 
