@@ -62,6 +62,11 @@ constexpr size_t BIG_ALIGN = 2u << 20;
 constexpr int MULTI_LEN[] = {32, 16, 8, 4, 2};
 constexpr int N_MULTI = (int)(sizeof(MULTI_LEN) / sizeof(MULTI_LEN[0]));
 
+// FP64 elements of a staging chunk (1 MiB): long enough that the host's copy
+// of one chunk (about 0.1-0.3 ms) covers the GPU's filling of the next,
+// short enough that pinning two of them at init costs nothing noticeable.
+constexpr int STAGE_ELEMS = 1 << 17;
+
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 int elem_bytes(int storage) { return storage == IBLB_F64 ? 8 : (storage == IBLB_F32 ? 4 : 2); }
@@ -100,7 +105,7 @@ struct Plan {
     // workspace offsets
     size_t off_boxes = 0, off_drops = 0, off_qh = 0, off_ql = 0, off_phi = 0, off_wgt = 0,
            off_trec = 0, off_tile_list = 0, off_tile_count = 0, off_part = 0, off_breg = 0,
-           off_base = 0, off_s0 = 0, off_bbox = 0, off_blk_drop = 0, off_tri = 0,
+           off_base = 0, off_s0 = 0, off_bbox = 0, off_blk_drop = 0, off_node_of = 0, off_tri = 0,
            off_csr_off = 0, off_csr_ent = 0, off_chunks = 0, off_tri_part = 0, off_rows = 0,
            off_tchunk = 0, off_tcand = 0, off_tncand = 0, off_scan = 0, off_ctr = 0, off_step_epoch = 0, off_status = 0, off_obs_groups = 0,
            off_obs_part = 0, off_obs_part1 = 0, off_obs_part2 = 0,
@@ -383,6 +388,7 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_breg = take((size_t)BREG * p.nblk * 4);
     p.off_part = take((size_t)3 * MAXP * p.nblk * p.real);
     p.off_blk_drop = take((size_t)p.nblk * 8);
+    p.off_node_of = take(N * 4);
     p.off_tri = take(3 * (size_t)p.Ttot * 4);
     p.off_csr_off = take((N + 1) * 4);
     p.off_csr_ent = take(3 * (size_t)p.Ttot * 4);
@@ -446,6 +452,8 @@ struct iblb_ctx {
     bool unstable = false;
     std::string err = "no error";
     double *host_obs = nullptr;  // pinned: the observables' kernels write it
+    double *stage[2] = {nullptr, nullptr};  // pinned chunks of STAGE_ELEMS (state in and out)
+    hipEvent_t ev_stage[2] = {nullptr, nullptr};
     std::vector<char> init_qh, init_ql;  // initial node positions, kept during init only
 };
 
@@ -939,34 +947,49 @@ void tune_store(const std::string &key, const Launch &L) {
         << '\n';
 }
 
-// ---- host conversion of stored populations (I/O only) ----
-double decode(const iblb_ctx *c, const void *raw, size_t i) {
-    switch (c->plan.storage) {
-    case IBLB_F64: return ((const double *)raw)[i];
-    case IBLB_F32: return ((const float *)raw)[i];
-    case IBLB_F16DEV: return (double)(float)((const _Float16 *)raw)[i] / c->plan.scale;
-    default: {
-        uint32_t bits = (uint32_t)((const uint16_t *)raw)[i] << 16;
-        float f;
-        std::memcpy(&f, &bits, 4);
-        return f;
+// ---- state in and out through the staging chunks ----
+// out[0 .. total) from the device: launch(e0, n, chunk) enqueues the kernel
+// that fills `chunk` with elements e0 .. e0 + n - 1; the host copies one
+// chunk out while the GPU fills the next.
+template <typename Launch>
+iblb_status stage_out(iblb_ctx *c, int64_t total, double *out, Launch launch) {
+    auto take = [&](int64_t k) -> iblb_status {
+        const int64_t e0 = k * STAGE_ELEMS;
+        HIPCHK(c, hipEventSynchronize(c->ev_stage[k & 1]));
+        std::memcpy(out + e0, c->stage[k & 1], (size_t)std::min<int64_t>(STAGE_ELEMS, total - e0) * 8);
+        return IBLB_OK;
+    };
+    const int64_t n = (total + STAGE_ELEMS - 1) / STAGE_ELEMS;
+    for (int64_t k = 0; k < n; ++k) {
+        const int64_t e0 = k * STAGE_ELEMS;
+        HIPCHK(c, launch(e0, (int)std::min<int64_t>(STAGE_ELEMS, total - e0), c->stage[k & 1]));
+        HIPCHK(c, hipEventRecord(c->ev_stage[k & 1], c->stream));
+        if (k > 0) {
+            const iblb_status st = take(k - 1);
+            if (st != IBLB_OK) return st;
+        }
     }
-    }
+    return n > 0 ? take(n - 1) : IBLB_OK;
 }
 
-void encode(const iblb_ctx *c, void *raw, size_t i, double v) {
-    switch (c->plan.storage) {
-    case IBLB_F64: ((double *)raw)[i] = v; break;
-    case IBLB_F32: ((float *)raw)[i] = (float)v; break;
-    case IBLB_F16DEV: ((_Float16 *)raw)[i] = (_Float16)(float)(v * c->plan.scale); break;
-    default: {
-        const float f = (float)v;
-        uint32_t bits;
-        std::memcpy(&bits, &f, 4);
-        bits += 0x7fffu + ((bits >> 16) & 1u);  // round to nearest even
-        ((uint16_t *)raw)[i] = (uint16_t)(bits >> 16);
+// Copy n finite values; false (with some of them copied) if one is not.
+// x - x is 0 for a finite x, NaN otherwise; eight sums let it vectorise.
+bool copy_finite(double *to, const double *from, size_t n) {
+    double bad[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    size_t k = 0;
+    for (; k + 8 <= n; k += 8)
+        for (int j = 0; j < 8; ++j) {
+            const double v = from[k + j];
+            to[k + j] = v;
+            bad[j] += v - v;
+        }
+    for (; k < n; ++k) {
+        to[k] = from[k];
+        bad[0] += from[k] - from[k];
     }
-    }
+    double s = 0;
+    for (double v : bad) s += v;
+    return s == 0.0;
 }
 
 inline int wrap(int i, int n) { return ((i % n) + n) % n; }
@@ -1023,6 +1046,7 @@ static iblb_status init_device(iblb_ctx *c) {
     P.breg = (int32_t *)at(p.off_breg);
     P.part = at(p.off_part);
     P.blk_drop = (int32_t *)at(p.off_blk_drop);
+    P.node_of = (int32_t *)at(p.off_node_of);
     P.tri = (int32_t *)at(p.off_tri);
     P.csr_off = (int32_t *)at(p.off_csr_off);
     P.csr_ent = (int32_t *)at(p.off_csr_ent);
@@ -1114,7 +1138,8 @@ static iblb_status init_device(iblb_ctx *c) {
     const int R = p.real;
     std::vector<char> qh((size_t)3 * N * R, 0), ql((size_t)3 * N * R, 0);
     std::vector<int32_t> tri((size_t)3 * std::max(p.Ttot, 1)), csr_off((size_t)N + 1, 0),
-        csr_ent((size_t)3 * std::max(p.Ttot, 1)), blk_drop(2 * (size_t)std::max(p.nblk, 1));
+        csr_ent((size_t)3 * std::max(p.Ttot, 1)), blk_drop(2 * (size_t)std::max(p.nblk, 1)),
+        node_of(std::max(N, 1), 0);
     std::vector<TriChunk> chunks(std::max(p.n_chunks, 1));
     std::vector<DropDev> dd(std::max<size_t>(p.drops.size(), 1));
     for (size_t di = 0; di < p.drops.size(); ++di) {
@@ -1147,6 +1172,7 @@ static iblb_status init_device(iblb_ctx *c) {
         }
         for (int k = 0; k < H.d.n_nodes; ++k) {
             const int j = H.node_off + k;
+            node_of[H.node_off + H.perm[k]] = j;
             for (int a = 0; a < 3; ++a) {
                 const double v = H.nodes[3 * H.perm[k] + a];
                 if (R == 8) {
@@ -1186,6 +1212,7 @@ static iblb_status init_device(iblb_ctx *c) {
     HIPCHK(c, hipMemcpyAsync(P.csr_off, csr_off.data(), csr_off.size() * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.csr_ent, csr_ent.data(), 3 * (size_t)p.Ttot * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.blk_drop, blk_drop.data(), (size_t)p.nblk * 8, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(P.node_of, node_of.data(), (size_t)N * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.chunks, chunks.data(), (size_t)p.n_chunks * sizeof(TriChunk), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.obs_groups, og.data(), og.size() * sizeof(ObsGroup), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.tchunk_box, tchunk.data(), tchunk.size() * 4, hipMemcpyHostToDevice, c->stream));
@@ -1246,10 +1273,13 @@ static iblb_status init_device(iblb_ctx *c) {
     c->init_ql = std::vector<char>();
     if (st == IBLB_OK) st = build_graphs(c);
     if (st == IBLB_OK) {
-        if (hipHostMalloc((void **)&c->host_obs,
-                          ((size_t)P.n_drops * OBS_DROP + (size_t)P.n_boxes * OBS_BOX) * 8 + 64,
-                          hipHostMallocDefault) != hipSuccess)
-            st = set_err(c, IBLB_E_DEVICE, "pinned host buffer allocation failed");
+        // one allocation: the staging chunks, then the observables
+        const size_t nobs = (size_t)P.n_drops * OBS_DROP + (size_t)P.n_boxes * OBS_BOX + 8;
+        if (hipHostMalloc((void **)&c->stage[0], (2 * (size_t)STAGE_ELEMS + nobs) * 8, hipHostMallocDefault) != hipSuccess)
+            return set_err(c, IBLB_E_DEVICE, "pinned host buffer allocation failed");
+        c->stage[1] = c->stage[0] + STAGE_ELEMS;
+        c->host_obs = c->stage[1] + STAGE_ELEMS;
+        for (hipEvent_t &e : c->ev_stage) HIPCHK(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
     return st;
 }
@@ -1467,13 +1497,6 @@ iblb_status iblb_observables(iblb_ctx *c, iblb_obs *per_drop, int32_t n_drops, i
     return IBLB_OK;
 }
 
-// Moving-wall term of population i reflected at the lower (z = 0) or upper
-// wall: 6 w_i rho0 (c_i . u_w).
-double wall_term(const iblb_box &b, int i, bool lower) {
-    const double *u = lower ? b.wall_lo : b.wall_hi;
-    return 6.0 * w_of(i) * b.rho0 * (cx_of(i) * u[0] + cy_of(i) * u[1]);
-}
-
 iblb_status iblb_read_window(iblb_ctx *c, int32_t box, const int32_t *lo, const int32_t *ext, double *f_out,
                              double *u_out) {
     if (!c) return set_err(nullptr, IBLB_E_INVAL, "ctx is NULL");
@@ -1493,44 +1516,11 @@ iblb_status iblb_read_window(iblb_ctx *c, int32_t box, const int32_t *lo, const 
     const size_t wcells = (size_t)ex * ey * ez;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (f_out) {
-        // the planes' rows from one cell below the window to one above it
-        // (every row when a periodic window touches the z ends)
-        const size_t eb = elem_bytes(c->plan.storage);
-        int za = lo[2] - 1, zb = lo[2] + ez;
-        if (zper && (za < 0 || zb >= nz)) {
-            za = 0;
-            zb = nz - 1;
-        }
-        za = std::max(za, 0);
-        zb = std::min(zb, nz - 1);
-        const size_t row = (size_t)H.sx * eb, slab = (size_t)(zb - za + 1) * ny * row;
-        std::vector<char> raw((size_t)Q * slab);
-        for (int i = 0; i < Q; ++i)
-            HIPCHK(c, hipMemcpy(raw.data() + (size_t)i * slab,
-                                c->ws + H.off_f[c->parity] + ((size_t)i * H.plane + (size_t)za * ny * H.sx) * eb, slab,
-                                hipMemcpyDeviceToHost));
-        const size_t pstride = slab / eb;  // elements per plane in raw
-        for (int wz = 0; wz < ez; ++wz)
-            for (int wy = 0; wy < ey; ++wy)
-                for (int wx = 0; wx < ex; ++wx) {
-                    const int z = zper ? wrap(lo[2] + wz, nz) : lo[2] + wz;
-                    const int y = wrap(lo[1] + wy, ny), x = wrap(lo[0] + wx, nx);
-                    const size_t cell = ((size_t)wz * ey + wy) * ex + wx;
-                    for (int i = 0; i < Q; ++i) {
-                        const int zs = z - cz_of(i);
-                        size_t src;
-                        double wall = 0.0;
-                        if (!zper && (zs < 0 || zs >= nz)) {
-                            src = (size_t)opp_of(i) * pstride + ((size_t)(z - za) * ny + y) * H.sx + x;
-                            wall = wall_term(H.b, i, zs < 0);
-                        } else {
-                            src = (size_t)i * pstride +
-                                  ((size_t)(wrap(zs, nz) - za) * ny + wrap(y - cy_of(i), ny)) * H.sx +
-                                  wrap(x - cx_of(i), nx);
-                        }
-                        f_out[(size_t)i * wcells + cell] = w_of(i) * H.b.rho0 + (decode(c, raw.data(), src) + wall);
-                    }
-                }
+        const Window W{{lo[0], lo[1], lo[2]}, {ex, ey, ez}};
+        const iblb_status st = stage_out(c, (int64_t)Q * wcells, f_out, [&](int64_t e0, int n, double *to) {
+            return launch_read_f(c->P, c->plan.storage, box, c->parity, W, c->plan.scale, e0, n, to, c->stream);
+        });
+        if (st != IBLB_OK) return st;
     }
     if (u_out && (c->plan.flags & IBLB_FLAG_FULL_U)) {
         const int R = c->plan.real;
@@ -1588,31 +1578,24 @@ iblb_status iblb_write_state(iblb_ctx *c, int32_t box, const double *f_in) {
     const BoxHost &H = c->plan.boxes[box];
     const int nx = H.b.nx, ny = H.b.ny, nz = H.b.nz;
     const size_t cells = (size_t)nx * ny * nz;
-    for (size_t k = 0; k < (size_t)Q * cells; ++k)
-        if (!std::isfinite(f_in[k])) return set_err(c, IBLB_E_INVAL, "populations not finite");
-    const size_t eb = elem_bytes(c->plan.storage);
-    std::vector<char> raw((size_t)Q * H.plane * eb, 0);
-    const bool zper = H.b.zbc == IBLB_Z_PERIODIC;
-    // inverse of the pull: the stored value at (i, y) is f_i(y + c_i), or,
-    // where y + c_i lies in a wall, f_opp(i)(y)
-    for (int z = 0; z < nz; ++z)
-        for (int y = 0; y < ny; ++y)
-            for (int x = 0; x < nx; ++x)
-                for (int i = 0; i < Q; ++i) {
-                    const int zt = z + cz_of(i);
-                    double v;
-                    if (!zper && (zt < 0 || zt >= nz))
-                        v = f_in[(size_t)opp_of(i) * cells + ((size_t)z * ny + y) * nx + x] -
-                            wall_term(H.b, opp_of(i), zt < 0);
-                    else
-                        v = f_in[(size_t)i * cells +
-                                 ((size_t)wrap(zt, nz) * ny + wrap(y + cy_of(i), ny)) * nx +
-                                 wrap(x + cx_of(i), nx)];
-                    encode(c, raw.data(), (size_t)i * H.plane + ((size_t)z * ny + y) * H.sx + x,
-                           v - w_of(i) * H.b.rho0);
-                }
+    // into the buffer the next step writes (nothing reads it before), so that
+    // a value that is not finite leaves the state as it was; then copied over
+    const int64_t total = (int64_t)Q * cells;
+    const int to = c->parity ^ 1;
+    for (int64_t k = 0; k * STAGE_ELEMS < total; ++k) {
+        const int64_t e0 = k * STAGE_ELEMS;
+        const int n = (int)std::min<int64_t>(STAGE_ELEMS, total - e0);
+        if (k > 1) HIPCHK(c, hipEventSynchronize(c->ev_stage[k & 1]));
+        if (!copy_finite(c->stage[k & 1], f_in + e0, (size_t)n)) {
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+            return set_err(c, IBLB_E_INVAL, "populations not finite");
+        }
+        HIPCHK(c, launch_write_f(c->P, c->plan.storage, box, to, c->plan.scale, e0, n, c->stage[k & 1], c->stream));
+        HIPCHK(c, hipEventRecord(c->ev_stage[k & 1], c->stream));
+    }
+    HIPCHK(c, hipMemcpyAsync(c->ws + H.off_f[c->parity], c->ws + H.off_f[to],
+                             (size_t)Q * H.plane * elem_bytes(c->plan.storage), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipMemcpy(c->ws + H.off_f[c->parity], raw.data(), raw.size(), hipMemcpyHostToDevice));
     return IBLB_OK;
 }
 
@@ -1624,19 +1607,9 @@ iblb_status iblb_read_nodes(iblb_ctx *c, int32_t d, double *nodes_out) {
         if (fst != IBLB_OK) return fst;
     }
     const DropHost &H = c->plan.drops[d];
-    const int N = c->P.Ntot, R = c->plan.real;
-    std::vector<char> qh((size_t)3 * N * R), ql((size_t)3 * N * R);
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    HIPCHK(c, hipMemcpy(qh.data(), c->P.qh, qh.size(), hipMemcpyDeviceToHost));
-    HIPCHK(c, hipMemcpy(ql.data(), c->P.ql, ql.size(), hipMemcpyDeviceToHost));
-    for (int k = 0; k < H.d.n_nodes; ++k)
-        for (int a = 0; a < 3; ++a) {
-            const size_t idx = (size_t)a * N + H.node_off + k;
-            nodes_out[3 * (size_t)H.perm[k] + a] =
-                R == 8 ? ((double *)qh.data())[idx] + ((double *)ql.data())[idx]
-                       : (double)((float *)qh.data())[idx] + (double)((float *)ql.data())[idx];
-        }
-    return IBLB_OK;
+    return stage_out(c, 3 * (int64_t)H.d.n_nodes, nodes_out, [&](int64_t e0, int n, double *to) {
+        return launch_read_q(c->P, is_f64(c), H.node_off, e0, n, to, c->stream);
+    });
 }
 
 iblb_status iblb_write_nodes(iblb_ctx *c, int32_t d, const double *nodes_in) {
@@ -2105,7 +2078,9 @@ iblb_status iblb_destroy(iblb_ctx *c) {
     if (c->ev_join) (void)hipEventDestroy(c->ev_join);
     if (c->ev_chain) (void)hipEventDestroy(c->ev_chain);
     if (c->ev_bulk) (void)hipEventDestroy(c->ev_bulk);
-    if (c->host_obs) (void)hipHostFree(c->host_obs);
+    for (hipEvent_t e : c->ev_stage)
+        if (e) (void)hipEventDestroy(e);
+    if (c->stage[0]) (void)hipHostFree(c->stage[0]);
     delete c;
     return IBLB_OK;
 }

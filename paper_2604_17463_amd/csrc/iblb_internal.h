@@ -193,6 +193,7 @@ struct DevPtrs {
     int32_t *breg;              // [nblk][BREG]: partial region x0,y0,z0 (wrapped), ex,ey,ez, overflow
     void *part;                 // [nblk][3][MAXP] partial spread regions (Real)
     int32_t *blk_drop;          // [nblk][2]: droplet and box of each node block
+    int32_t *node_of;           // [Ntot] per droplet: caller's node id -> global node id
     int32_t *tri;               // [Ttot][3] global node ids
     int32_t *csr_off;           // [Ntot+1]
     int32_t *csr_ent;           // [3 Ttot]: 3*t + corner
@@ -245,6 +246,18 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 // Observables of the current state into `out` (pinned host memory): per
 // droplet OBS_DROP values, per box OBS_BOX, then the status word.
 hipError_t launch_obs(const DevPtrs &P, int storage, int parity, float inv_scale, double *out, hipStream_t s);
+
+// A window of a box: ext cells along x, y, z from lo.
+struct Window {
+    int32_t lo[3], ext[3];
+};
+// State in and out, n FP64 elements from element e0, through host memory the
+// device can reach.
+hipError_t launch_read_f(const DevPtrs &P, int storage, int box, int parity, const Window &W, double scale, int64_t e0,
+                         int n, double *out, hipStream_t s);
+hipError_t launch_write_f(const DevPtrs &P, int storage, int box, int to, double scale, int64_t e0, int n,
+                          const double *in, hipStream_t s);
+hipError_t launch_read_q(const DevPtrs &P, bool f64, int node_off, int64_t e0, int n, double *out, hipStream_t s);
 
 // vol, area, zmin, zmax, cx, cy, cz, rsum, count, then the volume moments
 // about the node mean m: V, int (x-m), int (x-m)(x-m)^T (xx yy zz xy xz yz)

@@ -2,7 +2,8 @@
 // the node pass (interface forces, Peskin weights, tile stamps and the
 // block-partial spread), the stamped-tile list, interpolation with forward
 // Euler advection, and the inside bits of the viscosity contrast; and the
-// observables (iblb_obs.h).
+// observables (iblb_obs.h) and the state's way in and out (iblb_io.h).
+#include "iblb_io.h"
 #include "iblb_obs.h"
 
 namespace iblb {
