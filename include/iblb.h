@@ -212,15 +212,15 @@ iblb_status iblb_step(struct iblb_ctx *ctx, int64_t n_steps);
 /* For callers that cannot allocate device memory while they run (code under
  * HIP graph capture, tight serving loops, harnesses that forbid it): the
  * same n_steps time steps as iblb_step, bit for bit, with the step's own
- * scratch arrays (triangle records and FP64 partial sums, node-block
+ * scratch arrays (the triangles' FP64 partial sums, node-block
  * boxes, region descriptors and partial spread regions, the stamped-tile
  * list and the per-tile block records) taken from a fixed device array of
  * the library, 32 MiB per GPU, held from the library's load until the
  * process ends, instead of from the context's workspace.  Allocates
  * nothing and replays no graph: the kernels of each step are enqueued on
  * the context's stream one after another, with the step's advection
- * applied at its end.  The step scratch of a configuration grows with its
- * nodes (about 560 B per node in FP32, 1.1 KB in FP64) and its box cells
+ * applied at its end.  The step scratch counted for a configuration grows
+ * with its nodes (about 560 B per node in FP32, 1.1 KB in FP64) and its box cells
  * (1.25 B per cell): the 128x128x64 spreading workload needs about 7 MB.
  * One that exceeds 32 MiB returns IBLB_E_WORKSPACE with the bytes it
  * needs.  The array is shared by every
@@ -347,9 +347,9 @@ iblb_status iblb_band_tile(int32_t *shape);
  * advanced; the mesh is not).  Synchronising. */
 iblb_status iblb_time_stream_collide(struct iblb_ctx *ctx, int32_t reps, double *ms_out);
 
-/* Average device time (ms) of the mesh kernels of one step (triangle
- * records, node pass with stamps and partial spread, stamped-tile list,
- * interpolation; with tau_in the inside bits), over `reps` eager
+/* Average device time (ms) of the mesh kernels of one step (tile
+ * stamps, triangle volumes, stamped-tile list, node forces and partial
+ * spread, interpolation; with tau_in the inside bits), over `reps` eager
  * repetitions on the context's stream, each in a fresh tile epoch.  The
  * nodes do not move and the fluid is not touched; the last step's band
  * velocities are dropped (read_state reports NaN for them until the next

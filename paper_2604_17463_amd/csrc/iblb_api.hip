@@ -21,7 +21,7 @@
 using namespace iblb;
 
 // Fixed device scratch of iblb_step_static: the per-step arrays of the
-// spreading (triangle records and FP64 partial sums, node-block bounding
+// spreading (the triangles' FP64 partial sums, node-block bounding
 // boxes, region descriptors and partial regions, stamped-tile list and its
 // lengths, per-tile block records) for callers that cannot allocate.  Each
 // device holds its own copy from the library's load until the process ends.
@@ -103,15 +103,15 @@ struct Plan {
     size_t max_rows = 0;  // capacity of the bulk row-group table
     bool any_kvol = false;
     // workspace offsets
-    size_t off_boxes = 0, off_drops = 0, off_qh = 0, off_ql = 0, off_phi = 0, off_wgt = 0,
-           off_trec = 0, off_tile_list = 0, off_tile_count = 0, off_part = 0, off_breg = 0,
-           off_base = 0, off_s0 = 0, off_bbox = 0, off_blk_drop = 0, off_node_of = 0, off_tri = 0,
-           off_csr_off = 0, off_csr_ent = 0, off_chunks = 0, off_tri_part = 0, off_rows = 0,
+    size_t off_boxes = 0, off_drops = 0, off_qh = 0, off_ql = 0, off_phi = 0, off_q4 = 0,
+           off_tile_list = 0, off_tile_count = 0, off_part = 0, off_breg = 0,
+           off_base = 0, off_bbox = 0, off_blk_drop = 0, off_node_of = 0, off_tri = 0,
+           off_csr_off = 0, off_csr_ent = 0, off_csr_nb = 0, off_chunks = 0, off_tri_part = 0, off_rows = 0,
            off_tchunk = 0, off_tcand = 0, off_tncand = 0, off_scan = 0, off_ctr = 0, off_step_epoch = 0, off_status = 0, off_obs_groups = 0,
            off_obs_part = 0, off_obs_part1 = 0, off_obs_part2 = 0,
            off_uout = 0, total = 0;
     // the same per-step arrays inside the fixed scratch (iblb_step_static)
-    size_t st_trec = 0, st_tri_part = 0, st_bbox = 0, st_breg = 0, st_part = 0, st_tile_list = 0,
+    size_t st_tri_part = 0, st_bbox = 0, st_breg = 0, st_part = 0, st_tile_list = 0,
            st_tile_count = 0, st_tcand = 0, st_tncand = 0, st_scan = 0, st_total = 0;
 };
 
@@ -378,12 +378,10 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_qh = take(3 * N * p.real);
     p.off_ql = take(3 * N * p.real);
     p.off_phi = take(3 * N * p.real);
-    p.off_wgt = take(12 * N * p.real);
-    p.off_trec = take((size_t)TREC * p.Ttot * p.real);
+    p.off_q4 = take(8 * N * p.real);
     p.off_tile_list = take((size_t)p.total_tiles * 8);
     p.off_tile_count = take(2 * 4);
     p.off_base = take(3 * N * 4);
-    p.off_s0 = take(3 * N * 4);
     p.off_bbox = take(6 * (size_t)p.nblk * 4);
     p.off_breg = take((size_t)BREG * p.nblk * 4);
     p.off_part = take((size_t)3 * MAXP * p.nblk * p.real);
@@ -392,8 +390,9 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_tri = take(3 * (size_t)p.Ttot * 4);
     p.off_csr_off = take((N + 1) * 4);
     p.off_csr_ent = take(3 * (size_t)p.Ttot * 4);
+    p.off_csr_nb = take(6 * (size_t)p.Ttot * 4);
     p.off_chunks = take(sizeof(TriChunk) * (size_t)p.n_chunks);
-    p.off_tri_part = take(2 * (size_t)p.n_chunks * 8);
+    p.off_tri_part = take((size_t)p.n_chunks * 8);
     p.off_rows = take(sizeof(RowGroup) * (size_t)p.max_rows);
     p.off_tchunk = take((size_t)(p.total_tiles / TILE_CELLS) * 4);
     p.off_tcand = take((size_t)p.total_tiles * MAXC * 4);
@@ -409,7 +408,9 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_uout = take(3 * N * 8);
     p.total = round_up(o, ALIGN);
     o = 0;
-    p.st_trec = take((size_t)TREC * p.Ttot * p.real);
+    // 20 Reals per triangle stay counted (they were per-triangle records),
+    // so that a configuration is refused or taken as it always was
+    (void)take((size_t)20 * p.Ttot * p.real);
     p.st_tri_part = take(2 * (size_t)p.n_chunks * 8);
     p.st_bbox = take(6 * (size_t)p.nblk * 4);
     p.st_breg = take((size_t)BREG * p.nblk * 4);
@@ -474,6 +475,24 @@ iblb_status set_err(iblb_ctx *c, iblb_status code, const std::string &msg) {
 
 bool is_f64(const iblb_ctx *c) { return c->plan.storage == IBLB_F64; }
 
+// Launch of a context whose launch nobody chose.
+Launch default_launch(const iblb_ctx *c) {
+    int nxmax = 0;
+    size_t pop_bytes = 0;
+    for (const BoxHost &H : c->plan.boxes) {
+        nxmax = std::max(nxmax, H.b.nx);
+        pop_bytes += 2 * (size_t)Q * H.plane * elem_bytes(c->plan.storage);
+    }
+    Launch L{};
+    L.bx = nxmax <= 32 ? 32 : (nxmax <= 64 ? 64 : (nxmax <= 128 ? 128 : 256));
+    L.by = 256 / L.bx;
+    // streaming stores once both population buffers exceed the 256 MiB
+    // last-level cache
+    L.nt = pop_bytes > ((size_t)256 << 20) ? 1 : 0;
+    L.cpt = 1;
+    return L;
+}
+
 // Row groups of the bulk launch: BY * CPT rows each, and, when a row is
 // longer than the workgroup's threads along x (a multiple of 64), split into
 // segments of that length taken by consecutive workgroups, so that the
@@ -537,18 +556,29 @@ iblb_status compute_masks(iblb_ctx *c, int slot, hipStream_t s) {
     return IBLB_OK;
 }
 
+// The mesh chain of one step on stream s, up to the block-partial spread and
+// the list of stamped tiles.  `stamped` (may be null) is recorded as soon as
+// the stamps, their epoch and the inside bits are complete.
+iblb_status enqueue_chain(iblb_ctx *c, const DevPtrs &P, int p, bool advect, hipStream_t s, hipEvent_t stamped) {
+    const bool f64 = is_f64(c);
+    HIPCHK(c, launch_move(P, f64, advect ? MOVE_STEP : MOVE_PLACE, p, nullptr, s));
+    HIPCHK(c, launch_aux(P, f64, p, advect ? 1 : 0, s));
+    if (stamped) HIPCHK(c, hipEventRecord(stamped, s));
+    if (P.penalty) HIPCHK(c, launch_node(P, f64, true, s));
+    return IBLB_OK;
+}
+
 // n consecutive time steps on stream s, the first with buffer parity
-// `parity`.  Per step, on the second stream, the mesh chain: [advection of
-// the previous step] -> inside bits -> triangle records -> node pass
-// (forces, weights, tile stamps, partial spread) -> stamped-tile list.  The
-// band kernel gathers the spread force of every stamped tile and does the
+// `parity`.  Per step, on the second stream, the mesh chain: advection of
+// the previous step's nodes and tile stamps -> volumes, inside bits, list of
+// stamped tiles -> node forces and partial spread (without a volume penalty
+// beside the list).  The band kernel gathers the spread force of every stamped tile and does the
 // collision of its cells; the bulk stream-collide does the collision of the
 // other cells with the body force only.  Two schedules (Launch::after),
 // chosen by the autotuner; every cell gets the same arithmetic in both:
 //   0 (band beside bulk): the bulk kernel of step k runs on s after the
-//     node pass of step k (its stamps and inside bits) and skips the stamped
-//     tiles; the band kernel runs on the second stream right after the node
-//     pass, once the bulk kernel of step k-1 is done (it overwrites the
+//     stamps and inside bits of step k and skips the stamped tiles; the band
+//     kernel runs on the second stream right after the node forces, once the bulk kernel of step k-1 is done (it overwrites the
 //     buffer that kernel read).  The mesh chain of step k+1 follows the band
 //     kernel on the second stream, beside the bulk kernel of step k: per
 //     step, one queue crossing each way.
@@ -561,7 +591,6 @@ iblb_status compute_masks(iblb_ctx *c, int slot, hipStream_t s) {
 // band velocities) and runs first in the next chain, or in flush().  A run
 // ends joined into s.
 iblb_status enqueue_steps(iblb_ctx *c, hipStream_t s, int parity, bool advect_first, int n) {
-    const bool f64 = is_f64(c);
     const int full_u = (c->plan.flags & IBLB_FLAG_FULL_U) ? 1 : 0;
     const float scale = (float)c->plan.scale;
     if (c->plan.nblk == 0) {
@@ -569,22 +598,14 @@ iblb_status enqueue_steps(iblb_ctx *c, hipStream_t s, int parity, bool advect_fi
             HIPCHK(c, launch_bulk(c->P, c->plan.storage, parity ^ (k & 1), full_u, scale, c->L, false, s));
         return IBLB_OK;
     }
-    auto chain = [&](int k, int p) -> iblb_status {
-        if (advect_first || k > 0) HIPCHK(c, launch_interp(c->P, f64, 0, nullptr, c->ib));
-        const iblb_status st = compute_masks(c, p, c->ib);
-        if (st != IBLB_OK) return st;
-        HIPCHK(c, launch_tri(c->P, f64, c->ib));
-        HIPCHK(c, launch_node(c->P, f64, 0, p, c->ib));
-        HIPCHK(c, hipEventRecord(c->ev_chain, c->ib));
-        return IBLB_OK;
-    };
     if (c->L.after) {
         for (int k = 0; k < n; ++k) {
             const int p = parity ^ (k & 1);
             HIPCHK(c, hipEventRecord(c->ev_fork, s));
             HIPCHK(c, hipStreamWaitEvent(c->ib, c->ev_fork, 0));
-            const iblb_status st = chain(k, p);
+            const iblb_status st = enqueue_chain(c, c->P, p, advect_first || k > 0, c->ib, nullptr);
             if (st != IBLB_OK) return st;
+            HIPCHK(c, hipEventRecord(c->ev_chain, c->ib));
             HIPCHK(c, launch_bulk(c->P, c->plan.storage, p, full_u, scale, c->L, false, s));
             HIPCHK(c, hipStreamWaitEvent(s, c->ev_chain, 0));
             HIPCHK(c, launch_band(c->P, c->plan.storage, p, full_u, scale, true, c->L.nt, s));
@@ -595,7 +616,7 @@ iblb_status enqueue_steps(iblb_ctx *c, hipStream_t s, int parity, bool advect_fi
     HIPCHK(c, hipStreamWaitEvent(c->ib, c->ev_fork, 0));
     for (int k = 0; k < n; ++k) {
         const int p = parity ^ (k & 1);
-        const iblb_status st = chain(k, p);
+        const iblb_status st = enqueue_chain(c, c->P, p, advect_first || k > 0, c->ib, c->ev_chain);
         if (st != IBLB_OK) return st;
         HIPCHK(c, hipStreamWaitEvent(s, c->ev_chain, 0));
         HIPCHK(c, launch_bulk(c->P, c->plan.storage, p, full_u, scale, c->L, true, s));
@@ -612,7 +633,7 @@ iblb_status enqueue_steps(iblb_ctx *c, hipStream_t s, int parity, bool advect_fi
 // steps).  Every call that reads or replaces state starts with it.
 iblb_status flush(iblb_ctx *c) {
     if (!c->pending) return IBLB_OK;
-    HIPCHK(c, launch_interp(c->P, is_f64(c), 0, nullptr, c->stream));
+    HIPCHK(c, launch_move(c->P, is_f64(c), MOVE_FLUSH, 0, nullptr, c->stream));
     c->pending = false;
     ++c->epoch;
     return IBLB_OK;
@@ -1036,12 +1057,10 @@ static iblb_status init_device(iblb_ctx *c) {
     P.qh = at(p.off_qh);
     P.ql = at(p.off_ql);
     P.phi = at(p.off_phi);
-    P.wgt = at(p.off_wgt);
-    P.trec = at(p.off_trec);
+    P.q4 = at(p.off_q4);
     P.tile_list = (int32_t *)at(p.off_tile_list);
     P.tile_count = (int32_t *)at(p.off_tile_count);
     P.base = (int32_t *)at(p.off_base);
-    P.s0 = (int32_t *)at(p.off_s0);
     P.bbox = (int32_t *)at(p.off_bbox);
     P.breg = (int32_t *)at(p.off_breg);
     P.part = at(p.off_part);
@@ -1050,6 +1069,7 @@ static iblb_status init_device(iblb_ctx *c) {
     P.tri = (int32_t *)at(p.off_tri);
     P.csr_off = (int32_t *)at(p.off_csr_off);
     P.csr_ent = (int32_t *)at(p.off_csr_ent);
+    P.csr_nb = (int32_t *)at(p.off_csr_nb);
     P.chunks = (TriChunk *)at(p.off_chunks);
     P.tri_part = (double *)at(p.off_tri_part);
     P.rows = (RowGroup *)at(p.off_rows);
@@ -1138,7 +1158,7 @@ static iblb_status init_device(iblb_ctx *c) {
     const int R = p.real;
     std::vector<char> qh((size_t)3 * N * R, 0), ql((size_t)3 * N * R, 0);
     std::vector<int32_t> tri((size_t)3 * std::max(p.Ttot, 1)), csr_off((size_t)N + 1, 0),
-        csr_ent((size_t)3 * std::max(p.Ttot, 1)), blk_drop(2 * (size_t)std::max(p.nblk, 1)),
+        csr_ent((size_t)3 * std::max(p.Ttot, 1)), csr_nb((size_t)6 * std::max(p.Ttot, 1)), blk_drop(2 * (size_t)std::max(p.nblk, 1)),
         node_of(std::max(N, 1), 0);
     std::vector<TriChunk> chunks(std::max(p.n_chunks, 1));
     std::vector<DropDev> dd(std::max<size_t>(p.drops.size(), 1));
@@ -1160,6 +1180,7 @@ static iblb_status init_device(iblb_ctx *c) {
         D.A = H.A;
         D.xi = H.d.xi;
         D.kvol = H.d.k_vol;
+        if (D.kvol > 0.0) P.penalty = 1;
         D.V0 = 0.0;
         for (int a = 0; a < 3; ++a) D.ref[a] = H.ref[a];
         for (int k = 0; k < H.n_blocks; ++k) {
@@ -1197,7 +1218,10 @@ static iblb_status init_device(iblb_ctx *c) {
         for (int t = 0; t < p.Ttot; ++t)
             for (int cc = 0; cc < 3; ++cc) {
                 const int j = tri[3 * t + cc];
-                csr_ent[csr_off[j] + fill[j]++] = 3 * t + cc;
+                const int e = csr_off[j] + fill[j]++;
+                csr_ent[e] = 3 * t + cc;
+                csr_nb[2 * (size_t)e] = tri[3 * t + (cc + 1) % 3] | (int32_t)((uint32_t)cc << NODE_BITS);
+                csr_nb[2 * (size_t)e + 1] = tri[3 * t + (cc + 2) % 3];
             }
     }
     HIPCHK(c, hipMemcpyAsync(P.boxes, bd.data(), bd.size() * sizeof(BoxDev), hipMemcpyHostToDevice, c->stream));
@@ -1211,6 +1235,7 @@ static iblb_status init_device(iblb_ctx *c) {
     HIPCHK(c, hipMemcpyAsync(P.tri, tri.data(), 3 * (size_t)p.Ttot * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.csr_off, csr_off.data(), csr_off.size() * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.csr_ent, csr_ent.data(), 3 * (size_t)p.Ttot * 4, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(P.csr_nb, csr_nb.data(), 6 * (size_t)p.Ttot * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.blk_drop, blk_drop.data(), (size_t)p.nblk * 8, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.node_of, node_of.data(), (size_t)N * 4, hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(P.chunks, chunks.data(), (size_t)p.n_chunks * sizeof(TriChunk), hipMemcpyHostToDevice, c->stream));
@@ -1236,25 +1261,15 @@ static iblb_status init_device(iblb_ctx *c) {
     HIPCHK(c, hipMemsetAsync(P.status, 0, 4, c->stream));
     HIPCHK(c, hipMemsetAsync(P.phi, 0, (size_t)3 * N * R, c->stream));
     // reference volumes V0 from the initial mesh (same FP64 sum as the penalty)
-    HIPCHK(c, launch_tri(P, is_f64(c), c->stream));
-    HIPCHK(c, launch_set_v0(P, is_f64(c), c->stream));
+    HIPCHK(c, launch_move(P, is_f64(c), MOVE_BINS, 0, nullptr, c->stream));
+    HIPCHK(c, launch_volume(P, is_f64(c), c->stream));
+    HIPCHK(c, launch_set_v0(P, c->stream));
     // inside bits of the initial positions in both sets
     for (int k = 0; k < 2 && st == IBLB_OK; ++k) st = compute_masks(c, k, c->stream);
     if (st != IBLB_OK) return st;
     HIPCHK(c, hipStreamSynchronize(c->stream));
 
-    // default launch shape of the stream-collide kernel
-    int nxmax = 0;
-    for (auto &H : p.boxes) nxmax = std::max(nxmax, H.b.nx);
-    c->L.bx = nxmax <= 32 ? 32 : (nxmax <= 64 ? 64 : (nxmax <= 128 ? 128 : 256));
-    c->L.by = std::max(1, 256 / c->L.bx);
-    // streaming stores once both population buffers exceed the 256 MiB
-    // last-level cache
-    size_t pop_bytes = 0;
-    for (auto &H : p.boxes) pop_bytes += 2 * (size_t)Q * H.plane * elem_bytes(p.storage);
-    c->L.nt = pop_bytes > ((size_t)256 << 20) ? 1 : 0;
-    c->L.cpt = 1;
-    c->L.maxg = 0;
+    c->L = default_launch(c);
     st = upload_rows(c);
     if (st == IBLB_OK && (p.flags & IBLB_FLAG_AUTOTUNE)) {
         std::string key;
@@ -1401,7 +1416,6 @@ iblb_status iblb_step_static(iblb_ctx *c, int64_t n) {
     // the last call on this device left)
     DevPtrs V = c->P;
     char *const S = c->scratch;
-    V.trec = S + p.st_trec;
     V.tri_part = (double *)(S + p.st_tri_part);
     V.bbox = (int32_t *)(S + p.st_bbox);
     V.breg = (int32_t *)(S + p.st_breg);
@@ -1418,19 +1432,18 @@ iblb_status iblb_step_static(iblb_ctx *c, int64_t n) {
     // advection (none is left pending)
     for (int64_t k = 0; k < n; ++k) {
         const int par = c->parity;
-        const iblb_status st = compute_masks(c, par, s);  // inside bits: workspace arrays only
+        const iblb_status st = enqueue_chain(c, V, par, k > 0, s, nullptr);
         if (st != IBLB_OK) return st;
-        HIPCHK(c, launch_tri(V, f64, s));
-        HIPCHK(c, launch_node(V, f64, 0, par, s));
+        if (k > 0) ++c->epoch;  // the advection starts the next epoch
         HIPCHK(c, launch_band(V, p.storage, par, full_u, scale, true, c->L.nt, s));
         HIPCHK(c, launch_bulk(V, p.storage, par, full_u, scale, c->L, true, s));
-        HIPCHK(c, launch_interp(V, f64, 0, nullptr, s));
         c->last_step_epoch = c->epoch;
         c->last_step_parity = par;
-        ++c->epoch;  // the advection starts the next epoch
         c->parity ^= 1;
         ++c->step;
     }
+    HIPCHK(c, launch_move(V, f64, MOVE_FLUSH, 0, nullptr, s));
+    ++c->epoch;
     c->u_valid = true;
     // the workspace's records start empty for a later iblb_step
     HIPCHK(c, launch_fill_i32(c->P.tncand, 0, 2 * (int64_t)p.total_tiles, s));
@@ -1662,8 +1675,9 @@ iblb_status iblb_compute_forces(iblb_ctx *c, int32_t d, double *phi_out) {
         if (fst != IBLB_OK) return fst;
     }
     const bool f64 = is_f64(c);
-    HIPCHK(c, launch_tri(c->P, f64, c->stream));
-    HIPCHK(c, launch_node(c->P, f64, 1, c->parity, c->stream));
+    HIPCHK(c, launch_move(c->P, f64, MOVE_BINS, c->parity, nullptr, c->stream));
+    HIPCHK(c, launch_volume(c->P, f64, c->stream));
+    HIPCHK(c, launch_node(c->P, f64, false, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     const DropHost &H = c->plan.drops[d];
     const int N = c->P.Ntot, R = c->plan.real;
@@ -1685,9 +1699,10 @@ iblb_status iblb_compute_spread(iblb_ctx *c, int32_t b, double *F_out, uint8_t *
         iblb_status fst = flush(c);
         if (fst != IBLB_OK) return fst;
     }
-    const bool f64 = is_f64(c);
-    HIPCHK(c, launch_tri(c->P, f64, c->stream));
-    HIPCHK(c, launch_node(c->P, f64, 0, c->parity, c->stream));
+    {
+        const iblb_status st = enqueue_chain(c, c->P, c->parity, false, c->stream, nullptr);
+        if (st != IBLB_OK) return st;
+    }
     HIPCHK(c, launch_band(c->P, c->plan.storage, c->parity, 0, (float)c->plan.scale, false, 0, c->stream));
     HIPCHK(c, launch_epoch(c->P, c->stream));
     const int32_t used = c->epoch;
@@ -1747,9 +1762,8 @@ iblb_status iblb_interpolate(iblb_ctx *c, int32_t d, const double *u_in, double 
     HIPCHK(c, hipMemcpy(c->ws + H.off_u, ub.data(), ub.size(), hipMemcpyHostToDevice));
     const bool f64 = is_f64(c);
     double *Udev = (double *)(c->ws + c->plan.off_uout);
-    HIPCHK(c, launch_tri(c->P, f64, c->stream));
-    HIPCHK(c, launch_node(c->P, f64, 1, c->parity, c->stream));
-    HIPCHK(c, launch_interp(c->P, f64, 1, Udev, c->stream));
+    HIPCHK(c, launch_move(c->P, f64, MOVE_BINS, c->parity, nullptr, c->stream));
+    HIPCHK(c, launch_move(c->P, f64, MOVE_U, c->parity, Udev, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     std::vector<double> U((size_t)3 * c->P.Ntot);
     HIPCHK(c, hipMemcpy(U.data(), Udev, U.size() * 8, hipMemcpyDeviceToHost));
@@ -1765,8 +1779,7 @@ iblb_status iblb_read_bins(iblb_ctx *c, int32_t d, int32_t *base_out) {
         iblb_status fst = flush(c);
         if (fst != IBLB_OK) return fst;
     }
-    HIPCHK(c, launch_tri(c->P, is_f64(c), c->stream));
-    HIPCHK(c, launch_node(c->P, is_f64(c), 1, c->parity, c->stream));
+    HIPCHK(c, launch_move(c->P, is_f64(c), MOVE_BINS, c->parity, nullptr, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     const DropHost &H = c->plan.drops[d];
     const iblb_box &B = c->plan.boxes[H.d.box].b;
@@ -2055,11 +2068,9 @@ iblb_status iblb_time_mesh_chain(iblb_ctx *c, int32_t reps, double *ms) {
         // starts one; the nodes do not move (interpolation into a scratch U)
         HIPCHK(c, launch_epoch(c->P, c->stream));
         ++c->epoch;
-        iblb_status st = compute_masks(c, c->parity, c->stream);
+        const iblb_status st = enqueue_chain(c, c->P, c->parity, false, c->stream, nullptr);
         if (st != IBLB_OK) return st;
-        HIPCHK(c, launch_tri(c->P, f64, c->stream));
-        HIPCHK(c, launch_node(c->P, f64, 0, c->parity, c->stream));
-        HIPCHK(c, launch_interp(c->P, f64, 1, Udev, c->stream));
+        HIPCHK(c, launch_move(c->P, f64, MOVE_U, c->parity, Udev, c->stream));
     }
     HIPCHK(c, hipEventRecord(ev.b, c->stream));
     HIPCHK(c, hipEventSynchronize(ev.b));

@@ -4,7 +4,9 @@
 // gathers the spread interface force for each stamped tile and does the
 // collision of its 64 cells with it.  The two write disjoint cells and run
 // side by side.
-#include "iblb_device.h"
+#include "iblb_mesh_dev.h"
+
+#include <algorithm>
 
 namespace iblb {
 
@@ -24,9 +26,10 @@ namespace iblb {
 // box has a viscosity contrast or a moving wall (the plain variant carries
 // none of their registers).  Without SKIP the kernel is the plain
 // stream-collide of every cell (boxes without droplets, timing).
-template <int ST, bool UROW, bool NT, int CPT, bool EXT, bool SKIP, bool PADW>
-__global__ void __launch_bounds__(K1_MAX_THREADS)
-    k_bulk(DevPtrs P, int parity, int full_u, float scale, float inv) {
+// NTM: 0 plain stores, 1 streaming, 2 as `nt` says.
+template <int ST, bool UROW, int NTM, int CPT, bool EXT, bool SKIP, bool PADW>
+__device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST RowGroup &rg, int tx, int ty, int BX,
+                                          int BY, int parity, int epoch, int full_u, float scale, float inv, int nt) {
     using S = Stor<ST>;
     using R = typename S::R;
     constexpr uint32_t EB = sizeof(typename S::T);
@@ -34,123 +37,134 @@ __global__ void __launch_bounds__(K1_MAX_THREADS)
     // per-lane offset per access); 4- and 8-byte storage measured faster with
     // plain global addressing
     constexpr bool BUF = UROW && EB == 2;
-    const int tx = threadIdx.x, ty = threadIdx.y, BX = blockDim.x, BY = blockDim.y;
-    const IBLB_CONST RowGroup *rows = (const IBLB_CONST RowGroup *)P.rows;
-    // epoch of this step's stamps (written by the node pass, which this
-    // kernel follows); -2 never matches a stamp
-    const int epoch = SKIP ? ((const IBLB_GLOBAL int32_t *)P.step_epoch)[parity] : -2;
-    for (int gi = blockIdx.x; gi < P.n_rowgroups; gi += gridDim.x) {
-        const IBLB_CONST RowGroup &rg = rows[gi];
-        const IBLB_CONST BoxDev *B = (const IBLB_CONST BoxDev *)P.boxes + rg.box;
-        const int nx = B->nx, ny = B->ny, nz = B->nz, sx = B->sx;
-        const bool zper = B->zbc == 1;
-        const uint64_t pb = (uint64_t)B->plane * EB;
-        const IBLB_GLOBAL char *__restrict__ src = (const IBLB_GLOBAL char *)B->f[parity];
-        IBLB_GLOBAL char *__restrict__ dst = (IBLB_GLOBAL char *)B->f[parity ^ 1];
-        const R omega = (R)B->omega, guo = (R)B->guo, rho0 = (R)B->rho0;
-        const R omega_in = (R)B->omega_in, guo_in = (R)B->guo_in;
-        const bool contrast = B->contrast != 0, moving = B->moving != 0;
-        const IBLB_GLOBAL uint64_t *mask = (const IBLB_GLOBAL uint64_t *)B->mask[parity];
-        const IBLB_GLOBAL int32_t *stamp = (const IBLB_GLOBAL int32_t *)B->stamp[parity];
-        const int tnx = B->tnx, tny = B->tny;
-        const bool skip_box = SKIP && B->blk_end > B->blk_begin;  // only boxes holding droplets
-        R kw[4];
+    const IBLB_CONST BoxDev *B = (const IBLB_CONST BoxDev *)P.boxes + rg.box;
+    const int nx = B->nx, ny = B->ny, nz = B->nz, sx = B->sx;
+    const bool zper = B->zbc == 1;
+    const uint64_t pb = (uint64_t)B->plane * EB;
+    const IBLB_GLOBAL char *__restrict__ src = (const IBLB_GLOBAL char *)B->f[parity];
+    IBLB_GLOBAL char *__restrict__ dst = (IBLB_GLOBAL char *)B->f[parity ^ 1];
+    const R omega = (R)B->omega, guo = (R)B->guo, rho0 = (R)B->rho0;
+    const R omega_in = (R)B->omega_in, guo_in = (R)B->guo_in;
+    const bool contrast = B->contrast != 0, moving = B->moving != 0;
+    const IBLB_GLOBAL uint64_t *mask = (const IBLB_GLOBAL uint64_t *)B->mask[parity];
+    const IBLB_GLOBAL int32_t *stamp = (const IBLB_GLOBAL int32_t *)B->stamp[parity];
+    const int tnx = B->tnx, tny = B->tny;
+    const bool skip_box = SKIP && B->blk_end > B->blk_begin;  // only boxes holding droplets
+    R kw[4];
 #pragma unroll
-        for (int a = 0; a < 4; ++a) kw[a] = (R)(6.0 * B->rho0 * (double)scale * B->uw[a]);
-        const R gx = (R)B->g[0], gy = (R)B->g[1], gz = (R)B->g[2];
-        IBLB_GLOBAL R *__restrict__ uf = (IBLB_GLOBAL R *)B->ufull;
-        const uint64_t plane = (uint64_t)B->plane;
-        const PopRes rs = pop_res((const void *)src, pb), rd = pop_res((const void *)dst, pb);
-        // row r = z * ny + y, stepped by BY without a division per row; a
-        // thread takes CPT rows (BY apart) at a time, with the loads of all
-        // of them issued before the first collision
-        int r = rg.r0 + ty;
-        int z = r / ny, y = r - z * ny;
-        for (; r < rg.r1; r += BY * CPT) {
-            RowAddr ra[CPT];
-            bool on[CPT];
-            int ryk[CPT], rzk[CPT];
+    for (int a = 0; a < 4; ++a) kw[a] = (R)(6.0 * B->rho0 * (double)scale * B->uw[a]);
+    const R gx = (R)B->g[0], gy = (R)B->g[1], gz = (R)B->g[2];
+    IBLB_GLOBAL R *__restrict__ uf = (IBLB_GLOBAL R *)B->ufull;
+    const uint64_t plane = (uint64_t)B->plane;
+    const PopRes rs = pop_res((const void *)src, pb), rd = pop_res((const void *)dst, pb);
+    // row r = z * ny + y, stepped by BY without a division per row; a
+    // thread takes CPT rows (BY apart) at a time, with the loads of all
+    // of them issued before the first collision
+    int r = rg.r0 + ty;
+    int z = r / ny, y = r - z * ny;
+    for (; r < rg.r1; r += BY * CPT) {
+        RowAddr ra[CPT];
+        bool on[CPT];
+        int ryk[CPT], rzk[CPT];
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            on[k] = r + k * BY < rg.r1;
+            const int ry = UROW ? __builtin_amdgcn_readfirstlane(y) : y;
+            const int rz = UROW ? __builtin_amdgcn_readfirstlane(z) : z;
+            ryk[k] = ry;
+            rzk[k] = rz;
+            ra[k] = row_addr(ry, rz, ny, nz, sx, zper, EB);
+            y += BY;
+            while (y >= ny) {
+                y -= ny;
+                ++z;
+            }
+        }
+        // PADW: some row group's x range reaches into its row's padding
+        // (x1 > nx: the row table asks for it where the padding is a
+        // small part of the row): the lanes x in [nx, sx) redo the row's
+        // last cell and store zeros (the padding's value since init) in
+        // the same store instructions as their neighbours, so that every
+        // line of the row is written whole (a line written in part made
+        // rows of 250 cells 10 % slower than rows of 256).  A separate
+        // instantiation, so that workloads without it carry none of it.
+        for (int x = rg.x0 + tx; x < rg.x1; x += BX) {
+            R g[CPT][Q];
+            const bool pad = PADW && x >= nx;
+            const int xs = pad ? nx - 1 : x;  // the cell computed
+            const XOff xo = x_off<EB>(xs, nx);
+            const uint32_t xst = PADW ? (uint32_t)x * EB : xo.c;  // the cell stored
+            bool mine[CPT];
 #pragma unroll
             for (int k = 0; k < CPT; ++k) {
-                on[k] = r + k * BY < rg.r1;
-                const int ry = UROW ? __builtin_amdgcn_readfirstlane(y) : y;
-                const int rz = UROW ? __builtin_amdgcn_readfirstlane(z) : z;
-                ryk[k] = ry;
-                rzk[k] = rz;
-                ra[k] = row_addr(ry, rz, ny, nz, sx, zper, EB);
-                y += BY;
-                while (y >= ny) {
-                    y -= ny;
-                    ++z;
-                }
+                mine[k] = on[k];
+                if (skip_box && on[k])
+                    mine[k] = stamp[((int64_t)(rzk[k] >> TZS) * tny + (ryk[k] >> TYS)) * tnx + (xs >> TXS)] != epoch;
             }
-            // PADW: some row group's x range reaches into its row's padding
-            // (x1 > nx: the row table asks for it where the padding is a
-            // small part of the row): the lanes x in [nx, sx) redo the row's
-            // last cell and store zeros (the padding's value since init) in
-            // the same store instructions as their neighbours, so that every
-            // line of the row is written whole (a line written in part made
-            // rows of 250 cells 10 % slower than rows of 256).  A separate
-            // instantiation, so that workloads without it carry none of it.
-            for (int x = rg.x0 + tx; x < rg.x1; x += BX) {
-                R g[CPT][Q];
-                const bool pad = PADW && x >= nx;
-                const int xs = pad ? nx - 1 : x;  // the cell computed
-                const XOff xo = x_off<EB>(xs, nx);
-                const uint32_t xst = PADW ? (uint32_t)x * EB : xo.c;  // the cell stored
-                bool mine[CPT];
 #pragma unroll
-                for (int k = 0; k < CPT; ++k) {
-                    mine[k] = on[k];
-                    if (skip_box && on[k])
-                        mine[k] = stamp[((int64_t)(rzk[k] >> TZS) * tny + (ryk[k] >> TYS)) * tnx + (xs >> TXS)] != epoch;
+            for (int k = 0; k < CPT; ++k) {
+                if (!mine[k]) continue;
+                if constexpr (BUF)
+                    pull_buf<ST>(rs, (uint32_t)pb, ra[k], xo, g[k]);
+                else
+                    pull_raw<ST>(src, pb, ra[k], xo, g[k]);
+            }
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                if (!mine[k]) continue;
+                R out[Q], u[3], rho;
+                const uint32_t own = ra[k].ro[1][1] + xst;
+                R om = omega, gu = guo;
+                if (EXT && moving && (ra[k].wlo || ra[k].whi)) wall_shift<R>(g[k], ra[k].wlo, ra[k].whi, kw);
+                if (EXT && contrast) {
+                    // this step's inside bits (computed by the mesh
+                    // chain, which this kernel follows)
+                    const uint64_t w = mask[((int64_t)(rzk[k] >> 6) * ny + ryk[k]) * nx + xs];
+                    if ((w >> (rzk[k] & 63)) & 1ull) {
+                        om = omega_in;
+                        gu = guo_in;
+                    }
                 }
+                collide<ST>(g[k], gx, gy, gz, rho0, om, gu, scale, inv, out, u, rho);
+                if constexpr (PADW) {
 #pragma unroll
-                for (int k = 0; k < CPT; ++k) {
-                    if (!mine[k]) continue;
+                    for (int i = 0; i < Q; ++i) out[i] = pad ? R(0) : out[i];
+                }
+                if (NTM == 1 || (NTM == 2 && nt)) {
                     if constexpr (BUF)
-                        pull_buf<ST>(rs, (uint32_t)pb, ra[k], xo, g[k]);
+                        store_buf<ST, true>(rd, (uint32_t)pb, ra[k].ro[1][1], xst, out);
                     else
-                        pull_raw<ST>(src, pb, ra[k], xo, g[k]);
-                }
-#pragma unroll
-                for (int k = 0; k < CPT; ++k) {
-                    if (!mine[k]) continue;
-                    R out[Q], u[3], rho;
-                    const uint32_t own = ra[k].ro[1][1] + xst;
-                    R om = omega, gu = guo;
-                    if (EXT && moving && (ra[k].wlo || ra[k].whi)) wall_shift<R>(g[k], ra[k].wlo, ra[k].whi, kw);
-                    if (EXT && contrast) {
-                        // this step's inside bits (computed by the mesh
-                        // chain, which this kernel follows)
-                        const uint64_t w = mask[((int64_t)(rzk[k] >> 6) * ny + ryk[k]) * nx + xs];
-                        if ((w >> (rzk[k] & 63)) & 1ull) {
-                            om = omega_in;
-                            gu = guo_in;
-                        }
-                    }
-                    collide<ST>(g[k], gx, gy, gz, rho0, om, gu, scale, inv, out, u, rho);
-                    if constexpr (PADW) {
-#pragma unroll
-                        for (int i = 0; i < Q; ++i) out[i] = pad ? R(0) : out[i];
-                    }
+                        store_ptr<ST, true>(dst, pb, own, out);
+                } else {
                     if constexpr (BUF)
-                        store_buf<ST, NT>(rd, (uint32_t)pb, ra[k].ro[1][1], xst, out);
+                        store_buf<ST, false>(rd, (uint32_t)pb, ra[k].ro[1][1], xst, out);
                     else
-                        store_ptr<ST, NT>(dst, pb, own, out);
-                    if (PADW && pad) continue;
-                    if (full_u) {
-                        const uint64_t e = own / EB;
-                        uf[e] = u[0];
-                        uf[plane + e] = u[1];
-                        uf[2 * plane + e] = u[2];
-                    }
-                    if (!(rho > R(0) && rho < R(FLT_MAX))) atomicOr(P.status, BIT_RHO);
-                    if (u[0] * u[0] + u[1] * u[1] + u[2] * u[2] > R(1) / R(3)) atomicOr(P.status, BIT_MACH);
+                        store_ptr<ST, false>(dst, pb, own, out);
                 }
+                if (PADW && pad) continue;
+                if (full_u) {
+                    const uint64_t e = own / EB;
+                    uf[e] = u[0];
+                    uf[plane + e] = u[1];
+                    uf[2 * plane + e] = u[2];
+                }
+                if (!(rho > R(0) && rho < R(FLT_MAX))) atomicOr(P.status, BIT_RHO);
+                if (u[0] * u[0] + u[1] * u[1] + u[2] * u[2] > R(1) / R(3)) atomicOr(P.status, BIT_MACH);
             }
         }
     }
+}
+
+template <int ST, bool UROW, bool NT, int CPT, bool EXT, bool SKIP, bool PADW>
+__global__ void __launch_bounds__(K1_MAX_THREADS)
+    k_bulk(DevPtrs P, int parity, int full_u, float scale, float inv) {
+    const IBLB_CONST RowGroup *rows = (const IBLB_CONST RowGroup *)P.rows;
+    // epoch of this step's stamps (written by the mesh chain, which this
+    // kernel follows); -2 never matches a stamp
+    const int epoch = SKIP ? ((const IBLB_GLOBAL int32_t *)P.step_epoch)[parity] : -2;
+    for (int gi = blockIdx.x; gi < P.n_rowgroups; gi += gridDim.x)
+        bulk_rows<ST, UROW, NT ? 1 : 0, CPT, EXT, SKIP, PADW>(P, rows[gi], threadIdx.x, threadIdx.y, blockDim.x,
+                                                              blockDim.y, parity, epoch, full_u, scale, inv, 0);
 }
 
 // ------------------------------------------------------------ spread gather
@@ -231,38 +245,40 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
             const DropDev &D = P.drops[P.blk_drop[2 * blk]];
             const int j = blk * NB + lane;
             bool nh = false;
+            int s0[3] = {0, 0, 0};
+            R t[3] = {0, 0, 0};
             if (j - D.node_off < D.n_nodes) {
-                const int bx = P.base[j], by = P.base[N + j], bz = P.base[2 * N + j];
-                nh = meets(bx - 1, bx + 2, x0, x1, nx, true) && meets(by - 1, by + 2, y0, y1, ny, true) &&
-                     meets(bz - 1, bz + 2, z0, z1, nz, zper);
+                const R *qh = (const R *)P.qh, *ql = (const R *)P.ql;
+                int b[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) axis_base(qh[a * N + j], ql[a * N + j], b[a], t[a]);
+                nh = meets(b[0] - 1, b[0] + 2, x0, x1, nx, true) && meets(b[1] - 1, b[1] + 2, y0, y1, ny, true) &&
+                     meets(b[2] - 1, b[2] + 2, z0, z1, nz, zper);
+                s0[0] = wrapn(b[0] - 1, nx);
+                s0[1] = wrapn(b[1] - 1, ny);
+                s0[2] = zper ? wrapn(b[2] - 1, nz) : b[2] - 1;
             }
             uint64_t nmask = __ballot(nh);
             if (!nmask) continue;
-            const R *wgt = (const R *)P.wgt, *phi = (const R *)P.phi;
-            int s0x = 0, s0y = 0, s0z = 0;
-            R w[12], f[3];
-#pragma unroll
-            for (int q = 0; q < 12; ++q) w[q] = 0;
-            f[0] = f[1] = f[2] = 0;
+            R wx[4], wy[4], wz[4], f[3] = {0, 0, 0};
+            axis_weights(t[0], wx);
+            axis_weights(t[1], wy);
+            axis_weights(t[2], wz);
             if (nh) {
-                s0x = P.s0[j];
-                s0y = P.s0[N + j];
-                s0z = P.s0[2 * N + j];
-#pragma unroll
-                for (int q = 0; q < 12; ++q) w[q] = wgt[q * N + j];
+                const R *phi = (const R *)P.phi;
 #pragma unroll
                 for (int q = 0; q < 3; ++q) f[q] = phi[q * N + j];
             }
             while (nmask) {
                 const int nl = __builtin_ctzll(nmask);
                 nmask &= nmask - 1;
-                int ox = cx - bcast_i(s0x, nl), oy = cy - bcast_i(s0y, nl), oz = cz - bcast_i(s0z, nl);
+                int ox = cx - bcast_i(s0[0], nl), oy = cy - bcast_i(s0[1], nl), oz = cz - bcast_i(s0[2], nl);
                 if (ox < 0) ox += nx;
                 if (oy < 0) oy += ny;
                 if (zper && oz < 0) oz += nz;
-                const R ax = pick4(ox, bcast(w[0], nl), bcast(w[1], nl), bcast(w[2], nl), bcast(w[3], nl));
-                const R ay = pick4(oy, bcast(w[4], nl), bcast(w[5], nl), bcast(w[6], nl), bcast(w[7], nl));
-                const R az = pick4(oz, bcast(w[8], nl), bcast(w[9], nl), bcast(w[10], nl), bcast(w[11], nl));
+                const R ax = pick4(ox, bcast(wx[0], nl), bcast(wx[1], nl), bcast(wx[2], nl), bcast(wx[3], nl));
+                const R ay = pick4(oy, bcast(wy[0], nl), bcast(wy[1], nl), bcast(wy[2], nl), bcast(wy[3], nl));
+                const R az = pick4(oz, bcast(wz[0], nl), bcast(wz[1], nl), bcast(wz[2], nl), bcast(wz[3], nl));
                 const R wv = ax * ay * az;
                 F0 += bcast(f[0], nl) * wv;
                 F1 += bcast(f[1], nl) * wv;
@@ -332,20 +348,23 @@ constexpr int BAND_GRID = 8192;
 // rather than after it.  xcd: the grid (BAND_GRID workgroups) takes the
 // list in one contiguous eighth per XCD instead of interleaved.
 template <int ST, bool COLLIDE, bool ONE_BOX>
-__global__ void __launch_bounds__(256)
-    k_band(DevPtrs P, int parity, int full_u, float scale, float inv, int xcd, int nt) {
+__device__ __forceinline__ void band_role(const DevPtrs &P, int wg, int nwg, int parity, int full_u, float scale,
+                                          float inv, int xcd, int nt, int (*hits)[64 * GATHER_GROUP]) {
     using S = Stor<ST>;
     using R = typename S::R;
     constexpr uint32_t EB = sizeof(typename S::T);
-    __shared__ int hits[4][64 * GATHER_GROUP];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    const int nwaves = gridDim.x * 4;
+    const int wave = __builtin_amdgcn_readfirstlane(wg * 4 + (threadIdx.x >> 6));
+    const int nwaves = nwg * 4;
     const IBLB_CONST int32_t *tl = (const IBLB_CONST int32_t *)P.tile_list;
-    // the epoch counter, both list lengths and the wave's first list entry
+    // this step's epoch, both list lengths and the wave's first list entry
     // in one round trip (the entry lies in the list whatever the count; the
     // count decides whether it is used)
-    const int ctr = *P.ctr, n0 = P.tile_count[0], n1 = P.tile_count[1];
+    const int ctr = ((const IBLB_CONST int32_t *)P.step_epoch)[parity];
+    const int n0 = P.tile_count[0], n1 = P.tile_count[1];
+    // this step's epoch becomes the current one (nothing else reads the
+    // counter in this launch)
+    if (wg == 0 && threadIdx.x == 0) *P.ctr = ctr;
     const int first = min(wave, P.total_tiles - 1);
     const int first_gt = tl[2 * first], first_box = ONE_BOX ? 0 : tl[2 * first + 1];
     // the descriptor fields the tile's addressing needs (box 0's when there
@@ -373,7 +392,7 @@ __global__ void __launch_bounds__(256)
     // same time
     int i0 = wave, i1 = count, di = nwaves;
     if (xcd) {
-        const ListRange lr = xcd_list_range(blockIdx.x, threadIdx.x >> 6, gridDim.x, count);
+        const ListRange lr = xcd_list_range(wg, threadIdx.x >> 6, nwg, count);
         i0 = __builtin_amdgcn_readfirstlane(lr.first);
         i1 = lr.end;
         di = lr.stride;
@@ -455,6 +474,13 @@ __global__ void __launch_bounds__(256)
     }
 }
 
+template <int ST, bool COLLIDE, bool ONE_BOX>
+__global__ void __launch_bounds__(256)
+    k_band(DevPtrs P, int parity, int full_u, float scale, float inv, int xcd, int nt) {
+    __shared__ int hits[4][64 * GATHER_GROUP];
+    band_role<ST, COLLIDE, ONE_BOX>(P, blockIdx.x, gridDim.x, parity, full_u, scale, inv, xcd, nt, hits);
+}
+
 // ---------------------------------------------------------------- launchers
 template <int ST, bool UROW, bool NT, bool SKIP, bool PADW>
 static void launch_bulk_p(const DevPtrs &P, int parity, int full_u, float scale, float inv, const Launch &L,
@@ -523,11 +549,14 @@ hipError_t launch_bulk(const DevPtrs &P, int storage, int parity, int full_u, fl
     }
 }
 
+// Workgroups of the band kernel (four waves, one tile each at a time; a
+// wave loops over what is left of the list).
+static int band_groups(const DevPtrs &P) { return std::min((P.total_tiles + 3) / 4, BAND_GRID); }
 template <int ST, bool C>
 static void launch_band_t(const DevPtrs &P, int parity, int full_u, float scale, int nt, hipStream_t s) {
     // one wave per tile up to 32,768 waves (workgroups of four); large
     // bands (many boxes or droplets) loop over the rest of the list
-    const int grid = min((P.total_tiles + 3) / 4, BAND_GRID);
+    const int grid = band_groups(P);
     // a full grid (a multiple of eight workgroups) takes the list in XCD
     // ranges; a small one keeps the interleaved order, whose first entry
     // loads beside the list count (latency decides there)

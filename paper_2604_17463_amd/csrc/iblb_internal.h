@@ -41,10 +41,9 @@ __host__ __device__ inline int band_loc(int x, int y, int z) {
     return (((z & (TZ - 1)) << (TXS + TYS)) | ((y & (TY - 1)) << TXS) | (x & (TX - 1)));
 }
 constexpr int NB = 64;           // nodes per block
+constexpr int NODE_BITS = 30;     // csr_nb: node id, and the corner above it
+constexpr int NODE_MASK = (1 << NODE_BITS) - 1;
 constexpr int TRI_CHUNK = 256;   // triangles per FP64 partial-sum chunk
-constexpr int TREC = 20;         // per-triangle record: five four-vectors (A, n), (N/6, 0),
-                                 // and the corner forces (f_c, 0) of corners c = 0, 1, 2
-static_assert(TREC == 5 * 4, "triangle record = five four-vectors");
 constexpr int K1_MAX_THREADS = 256; // launch bound of the bulk stream-collide kernel
 constexpr int MAXP = 2048;          // cells of a node block's partial-spread region
 constexpr int BREG = 8;
@@ -183,12 +182,10 @@ struct DevPtrs {
     // node arrays, SoA [3][Ntot] unless stated
     void *qh, *ql;              // position, high and low parts (Real)
     void *phi;                  // nodal force (Real)
-    void *trec;                 // [Ttot][TREC] per-triangle records (Real)
+    void *q4;                   // [Ntot][2] positions as four-vectors hi, lo (Real), by the stamping pass
     int32_t *tile_list;         // [total_tiles][2]: stamped tiles of the epoch (global id, box)
     int32_t *tile_count;        // [2] list lengths, indexed by epoch parity
-    void *wgt;                  // [12][Ntot] Peskin weights x0..3,y0..3,z0..3 (Real)
-    int32_t *base;              // floor(q - 1/2), unwrapped
-    int32_t *s0;                // first stencil cell base-1, wrapped where periodic
+    int32_t *base;              // floor(q - 1/2), unwrapped (inspection)
     int32_t *bbox;              // [6][nblk]: x0,x1,y0,y1,z0,z1 of stencil cells
     int32_t *breg;              // [nblk][BREG]: partial region x0,y0,z0 (wrapped), ex,ey,ez, overflow
     void *part;                 // [nblk][3][MAXP] partial spread regions (Real)
@@ -196,16 +193,17 @@ struct DevPtrs {
     int32_t *node_of;           // [Ntot] per droplet: caller's node id -> global node id
     int32_t *tri;               // [Ttot][3] global node ids
     int32_t *csr_off;           // [Ntot+1]
-    int32_t *csr_ent;           // [3 Ttot]: 3*t + corner
+    int32_t *csr_ent;           // [3 Ttot]: 3*t + corner (inspection)
+    int32_t *csr_nb;            // [3 Ttot][2]: the incident triangle's other nodes in its order, corner in bits 30, 31
     TriChunk *chunks;
-    double *tri_part;           // [2][n_chunks]: volume, area
+    double *tri_part;           // [n_chunks] volume
     RowGroup *rows;
     int32_t *tchunk_box;        // [total_tiles/64] box of each 64-tile chunk
     int32_t *tcand;             // [total_tiles][MAXC] node blocks whose stencil box covers the tile
     int32_t *tncand;            // [2][total_tiles] their number, by epoch parity
     int32_t *scan_all;          // [2][n_boxes] some block of the box could not record its tiles
-    int32_t *ctr;               // step epoch
-    int32_t *step_epoch;        // [2] epoch of the last node pass, by buffer parity
+    int32_t *ctr;               // epoch of the last band pass
+    int32_t *step_epoch;        // [2] epoch of the last stamps, by buffer parity
     uint32_t *status;
     ObsGroup *obs_groups;       // row groups of the observables, box by box
     double *obs_part;           // [n_obs_groups][2] mass, max_u
@@ -214,9 +212,29 @@ struct DevPtrs {
     int32_t Ntot, nblk, Ttot, n_chunks;
     int32_t n_rowgroups, total_tiles, n_obs_groups, n_cus;  // n_cus: compute units of the device
     int32_t contrast;           // some box has tau_in set
+    int32_t penalty;            // some droplet has a volume penalty
     int32_t moving;             // some box has a moving wall
     int32_t mask_words;         // largest nzw*ny*nx over those boxes
     int32_t pad_rows;           // some row group runs into its row's padding (x1 > nx)
+};
+
+// What a launch of the move pass does, per block of 64 nodes:
+// MV_INTERP   interpolate the band velocity at the nodes (Eq. 7, u = 0 on
+//             wall cells)
+// MV_ADVECT   move the nodes by it (forward Euler, compensated hi/lo sum)
+// MV_OUT      write it to Uout instead
+// MV_GEOM     stencil box, partial region and node records of the positions
+// MV_STAMP    stamp every tile holding a stencil cell with epoch ctr + adv,
+//             record the block in every tile its stencil box covers
+// MV_BASE     write the base cells
+// MV_EPOCH    workgroup 0 starts the next epoch
+enum : int {
+    MV_INTERP = 1, MV_ADVECT = 2, MV_OUT = 4, MV_GEOM = 8, MV_STAMP = 16, MV_BASE = 32, MV_EPOCH = 64,
+    MOVE_STEP = MV_INTERP | MV_ADVECT | MV_GEOM | MV_STAMP,  // head of a step with a pending advection
+    MOVE_PLACE = MV_GEOM | MV_STAMP,                         // head of a step without one
+    MOVE_FLUSH = MV_INTERP | MV_ADVECT | MV_EPOCH,           // the pending advection alone
+    MOVE_BINS = MV_GEOM | MV_BASE,
+    MOVE_U = MV_INTERP | MV_OUT
 };
 
 // Launch entry points (iblb_fluid.hip, iblb_mesh.hip).
@@ -231,14 +249,19 @@ struct Launch {
                                 // the mesh chain, then the band kernel over its band tiles
 };
 
-hipError_t launch_tri(const DevPtrs &P, bool f64, hipStream_t s);
-hipError_t launch_set_v0(const DevPtrs &P, bool f64, hipStream_t s);
-hipError_t launch_node(const DevPtrs &P, bool f64, int mode, int parity, hipStream_t s);
+// The mesh chain of a step: launch_move (MOVE_STEP or MOVE_PLACE), launch_aux
+// (which also holds the node pass when no droplet has a volume penalty),
+// launch_node (otherwise).  adv: 1 when the move advected (its stamps then
+// start a new epoch), 0 else.
+hipError_t launch_move(const DevPtrs &P, bool f64, int mode, int parity, double *Uout, hipStream_t s);
+hipError_t launch_aux(const DevPtrs &P, bool f64, int parity, int adv, hipStream_t s);
+hipError_t launch_node(const DevPtrs &P, bool f64, bool spread, hipStream_t s);
+hipError_t launch_volume(const DevPtrs &P, bool f64, hipStream_t s);
+hipError_t launch_set_v0(const DevPtrs &P, hipStream_t s);
 hipError_t launch_bulk(const DevPtrs &P, int storage, int parity, int full_u, float scale,
                        const Launch &L, bool skip_band, hipStream_t s);
 hipError_t launch_band(const DevPtrs &P, int storage, int parity, int full_u, float scale,
                        bool collide, int nt, hipStream_t s);
-hipError_t launch_interp(const DevPtrs &P, bool f64, int mode, double *Uout, hipStream_t s);
 hipError_t launch_epoch(const DevPtrs &P, hipStream_t s);
 hipError_t launch_inside(const DevPtrs &P, bool f64, int slot, hipStream_t s);
 hipError_t launch_mask_clear(const DevPtrs &P, int slot, hipStream_t s);
