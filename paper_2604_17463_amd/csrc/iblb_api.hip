@@ -493,6 +493,25 @@ Launch default_launch(const iblb_ctx *c) {
     return L;
 }
 
+// Least LDS of a workgroup of the mesh kernels, which holds them to one (more
+// than half of a compute unit's 160 KB) or two workgroups per compute unit
+// beside the bulk kernel.  Their waves mostly wait for memory, each in the
+// place of a bulk wave that would keep more of it in flight: as long as the
+// chain ends before the bulk kernel does, fewer at a time cost nothing.  One
+// per compute unit against no limit: 250x250x150 with 927 node blocks 300
+// against 311 us per step, 512x512x256 with 2,576 blocks 1,891 against 1,906;
+// but 64 boxes with 5,837 blocks on 28 M cells 1,053 against 1,052 us, and two
+// per compute unit 1,027: there one leaves the chain (about 40 us per 256
+// blocks) longer than the bulk kernel.  At most 256 blocks are one round in
+// any case and keep their latency.
+int mesh_lds(const iblb_ctx *c) {
+    if (c->plan.nblk <= 256) return 0;
+    double bulk_us = 0;
+    for (const BoxHost &H : c->plan.boxes) bulk_us += 2.0 * Q * H.plane * elem_bytes(c->plan.storage) / 5.5e6;
+    const double chain_us = 40.0 * c->plan.nblk / 256;
+    return chain_us < 0.6 * bulk_us ? 96 << 10 : 64 << 10;
+}
+
 // Row groups of the bulk launch: BY * CPT rows each, and, when a row is
 // longer than the workgroup's threads along x (a multiple of 64), split into
 // segments of that length taken by consecutive workgroups, so that the
@@ -1090,6 +1109,7 @@ static iblb_status init_device(iblb_ctx *c) {
     P.n_chunks = p.n_chunks;
     P.total_tiles = p.total_tiles;
     P.n_obs_groups = p.n_obs_groups;
+    P.mesh_lds = mesh_lds(c);
     {
         int dev = 0, cus = 0;
         HIPCHK(c, hipGetDevice(&dev));
@@ -1415,6 +1435,7 @@ iblb_status iblb_step_static(iblb_ctx *c, int64_t n) {
     // start empty are cleared by a fill kernel (the scratch keeps whatever
     // the last call on this device left)
     DevPtrs V = c->P;
+    V.mesh_lds = 0;  // one queue: nothing runs beside the mesh kernels
     char *const S = c->scratch;
     V.tri_part = (double *)(S + p.st_tri_part);
     V.bbox = (int32_t *)(S + p.st_bbox);

@@ -144,6 +144,14 @@ __device__ __forceinline__ bool meets(int lo, int hi, int t0, int t1, int n, boo
     return (l <= t1 && h >= t0) || (l <= t1 + n && h >= t0 + n);
 }
 
+// The same for `ext` cells from lo, lo in [0, n) on a periodic axis; no
+// branches.
+__device__ __forceinline__ bool meets_wrapped(int lo, int ext, int t0, int t1, int n, bool per) {
+    const int hi = lo + ext - 1;
+    const bool here = (lo <= t1) & (hi >= t0);
+    return here | (per & ((ext >= n) | ((lo <= t1 + n) & (hi >= t0 + n))));
+}
+
 // ------------------------------------------------------- pulled populations
 // Addressing of one x-row for the pull: byte offsets (32-bit, a plane is
 // < 4 GiB) of the 9 source rows (y - c_y, z - c_z) and the wall flags.

@@ -176,22 +176,30 @@ __global__ void __launch_bounds__(K1_MAX_THREADS)
 // for a block whose region did not fit, the nodes summed here one by one in
 // ascending order.  No atomics: the sum order per cell is fixed.
 //
-// The candidate blocks are the ones the node pass recorded for the tile
-// (sorted here); when the records are incomplete the bounding boxes of all
-// blocks of the box are tested, GATHER_GROUP x 64 at a time, their hits
-// going to a wave-private LDS list in ascending order.  Either way the
-// region descriptors and partial values of GATHER_BATCH blocks load side by
-// side.
-constexpr int GATHER_GROUP = SCAN_GROUP / 64;
+// The candidate blocks are the ones the move pass recorded for the tile
+// (sorted here); when the records are incomplete the stencil boxes of all
+// blocks of the box are tested, GROUP x 64 at a time.  Either way one
+// lane holds one block's region descriptor, loaded together and handed out
+// by lane reads, and the partial values of GATHER_BATCH blocks load side by
+// side.  Where a block of the batch has no region, the blocks are taken from
+// a list (the scan's in LDS) with their descriptors read one by one.
+//
+// GROUP: beside the bulk kernel one group at a time, because the band
+// kernel's waves share the compute units with the bulk kernel's and have to
+// fit where one of those has ended.  Four at a time took 103 VGPRs instead of
+// 82 and the steps became longer: shear 128x96x192 89 against 81 us,
+// 128x128x64 51 against 49 us; 250x250x150 (band kernel 65 -> 262 us).
+// Against tests that loaded each bound behind the one before it, the band
+// kernel of 160 blocks alone went from 14.2 to 11.8 us.
 constexpr int GATHER_BATCH = 4;
 
-template <typename R>
+template <typename R, int GROUP>
 __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxDev *B, int box, int gt,
                                          int slot, int x0, int x1, int y0, int y1, int z0, int z1, int cx,
                                          int cy, int cz, int *hits, R &F0, R &F1, R &F2) {
     const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
-    const int nb = P.nblk, N = P.Ntot;
+    const int N = P.Ntot;
     const bool zper = B->zbc == 1;
     const int nx = B->nx, ny = B->ny, nz = B->nz;
     const int b0 = B->blk_begin, b1 = B->blk_end;
@@ -287,6 +295,40 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
         }
     };
 
+    // the same for blocks that all have a partial region, whose descriptors
+    // sit in the lanes: block id(lane) with descriptor ra, rb.  Takes the
+    // lanes ln[0 .. n) in this order.
+    auto add_lanes = [&](const int (&ln)[GATHER_BATCH], int n, int4 ra, int4 rb, int blk_of) {
+        R v[GATHER_BATCH][3];
+#pragma unroll
+        for (int k = 0; k < GATHER_BATCH; ++k) {
+            v[k][0] = v[k][1] = v[k][2] = R(0);
+            if (k < n) {
+                const int l = ln[k];
+                int dx = cx - bcast_i(ra.x, l), dy = cy - bcast_i(ra.y, l), dz = cz - bcast_i(ra.z, l);
+                if (dx < 0) dx += nx;
+                if (dy < 0) dy += ny;
+                if (zper && dz < 0) dz += nz;
+                const int ex = bcast_i(ra.w, l), ey = bcast_i(rb.x, l), ez = bcast_i(rb.y, l);
+                if (dx < ex && dy < ey && dz >= 0 && dz < ez) {
+                    const int64_t c = (int64_t)bcast_i(blk_of, l) * 3 * MAXP + 3 * ((dz * ey + dy) * ex + dx);
+                    v[k][0] = part[c];
+                    v[k][1] = part[c + 1];
+                    v[k][2] = part[c + 2];
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < GATHER_BATCH; ++k) {
+            if (k < n) {
+                F0 += v[k][0];
+                F1 += v[k][1];
+                F2 += v[k][2];
+            }
+        }
+    };
+    const int4 *regs = (const int4 *)P.breg;  // two per block
+
     // the recorded candidates: count, flag and the MAXC slots (lane k holds
     // slot k) in one round trip
     const int ncand = ((const IBLB_CONST int32_t *)P.tncand)[(int64_t)slot * P.total_tiles + gt];
@@ -295,34 +337,74 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
     int mine = lane < MAXC ? P.tcand[(int64_t)gt * MAXC + lane] : INT_MAX;
     if (!scan && ncand <= MAXC) {
         mine = lane < ncand ? mine : INT_MAX;
+        // every candidate's descriptor in one more
+        const int bid = lane < ncand ? mine : b0;
+        const int4 ra = regs[2 * (int64_t)bid], rb = regs[2 * (int64_t)bid + 1];
         // rank of each lane's block among the candidates (the ids are distinct)
         int rank = 0;
         for (int k = 0; k < ncand; ++k) rank += __builtin_amdgcn_readlane(mine, k) < mine ? 1 : 0;
+        auto lane_of = [&](int r) {
+            const uint64_t m = __ballot(lane < ncand && rank == r);
+            return m ? (int)__builtin_ctzll(m) : 0;
+        };
+        const bool any_ovf = __ballot(lane < ncand && rb.z != 0) != 0;
         for (int r0 = 0; r0 < ncand; r0 += GATHER_BATCH) {
-            auto id = [&](int k) {
-                const uint64_t m = __ballot(lane < ncand && rank == r0 + k);
-                return m ? __builtin_amdgcn_readlane(mine, __builtin_ctzll(m)) : 0;
-            };
-            add_blocks(id, min(GATHER_BATCH, ncand - r0));
+            const int n = min(GATHER_BATCH, ncand - r0);
+            if (any_ovf) {
+                add_blocks([&](int k) { return __builtin_amdgcn_readlane(mine, lane_of(r0 + k)); }, n);
+                continue;
+            }
+            int ln[GATHER_BATCH];
+#pragma unroll
+            for (int k = 0; k < GATHER_BATCH; ++k) ln[k] = k < n ? lane_of(r0 + k) : 0;
+            add_lanes(ln, n, ra, rb, bid);
         }
         return;
     }
-    for (int kb = b0; kb < b1; kb += 64 * GATHER_GROUP) {
-        bool hit[GATHER_GROUP];
+    for (int kb = b0; kb < b1; kb += 64 * GROUP) {
+        // every block's descriptor first, then the tests (a test that loads
+        // only where the one before it passed waits once per test)
+        int4 ra[GROUP], rb[GROUP];
 #pragma unroll
-        for (int g = 0; g < GATHER_GROUP; ++g) {
-            const int mb = kb + 64 * g + lane;
-            hit[g] = mb < b1 &&
-                     meets(P.bbox[0 * nb + mb], P.bbox[1 * nb + mb], x0, x1, nx, true) &&
-                     meets(P.bbox[2 * nb + mb], P.bbox[3 * nb + mb], y0, y1, ny, true) &&
-                     meets(P.bbox[4 * nb + mb], P.bbox[5 * nb + mb], z0, z1, nz, zper);
+        for (int g = 0; g < GROUP; ++g) {
+            if (g > 0 && kb + 64 * g >= b1) continue;
+            const int mb = min(kb + 64 * g + lane, b1 - 1);
+            ra[g] = regs[2 * (int64_t)mb];
+            rb[g] = regs[2 * (int64_t)mb + 1];
+        }
+        uint64_t hit[GROUP], any_ovf = 0;
+#pragma unroll
+        for (int g = 0; g < GROUP; ++g) {
+            hit[g] = 0;
+            if (g > 0 && kb + 64 * g >= b1) continue;
+            const bool mx = meets_wrapped(ra[g].x, ra[g].w, x0, x1, nx, true);
+            const bool my = meets_wrapped(ra[g].y, rb[g].x, y0, y1, ny, true);
+            const bool mz = meets_wrapped(ra[g].z, rb[g].y, z0, z1, nz, zper);
+            hit[g] = __ballot(kb + 64 * g + lane < b1 && mx && my && mz);
+            any_ovf |= hit[g] & __ballot(rb[g].z != 0);
+        }
+        if (!any_ovf) {
+#pragma unroll
+            for (int g = 0; g < GROUP; ++g) {
+                uint64_t m = hit[g];
+                while (m) {
+                    const int n = min(GATHER_BATCH, (int)__popcll(m));
+                    int ln[GATHER_BATCH];
+#pragma unroll
+                    for (int k = 0; k < GATHER_BATCH; ++k) {
+                        ln[k] = k < n ? (int)__builtin_ctzll(m) : 0;
+                        m &= m - (k < n ? 1 : 0);
+                    }
+                    add_lanes(ln, n, ra[g], rb[g], kb + 64 * g + lane);
+                }
+            }
+            continue;
         }
         int total = 0;
 #pragma unroll
-        for (int g = 0; g < GATHER_GROUP; ++g) {
-            const uint64_t m = __ballot(hit[g]);
-            if (hit[g]) hits[total + __popcll(m & below)] = kb + 64 * g + lane;
-            total += __popcll(m);
+        for (int g = 0; g < GROUP; ++g) {
+            if ((hit[g] >> lane) & 1) hits[total + __popcll(hit[g] & below)] = kb + 64 * g + lane;
+            total += __popcll(hit[g]);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -347,9 +429,9 @@ constexpr int BAND_GRID = 8192;
 // ONE_BOX: a single box, whose descriptor is read beside the list entry
 // rather than after it.  xcd: the grid (BAND_GRID workgroups) takes the
 // list in one contiguous eighth per XCD instead of interleaved.
-template <int ST, bool COLLIDE, bool ONE_BOX>
+template <int ST, bool COLLIDE, bool ONE_BOX, int GROUP>
 __device__ __forceinline__ void band_role(const DevPtrs &P, int wg, int nwg, int parity, int full_u, float scale,
-                                          float inv, int xcd, int nt, int (*hits)[64 * GATHER_GROUP]) {
+                                          float inv, int xcd, int nt, int (*hits)[64 * GROUP]) {
     using S = Stor<ST>;
     using R = typename S::R;
     constexpr uint32_t EB = sizeof(typename S::T);
@@ -424,7 +506,7 @@ __device__ __forceinline__ void band_role(const DevPtrs &P, int wg, int nwg, int
             pull_buf<ST, true>(rs, (uint32_t)pb, ra, xo, g);
         }
         R F0 = 0, F1 = 0, F2 = 0;
-        gather_F<R>(P, B, box, gt, ctr & 1, x0, x1, y0, y1, z0, z1, cx, cy, cz, hits[threadIdx.x >> 6], F0,
+        gather_F<R, GROUP>(P, B, box, gt, ctr & 1, x0, x1, y0, y1, z0, z1, cx, cy, cz, hits[threadIdx.x >> 6], F0,
                     F1, F2);
         if (!COLLIDE) {
             IBLB_GLOBAL R *Fb = (IBLB_GLOBAL R *)B->Fband + (int64_t)lt * 3 * TILE_CELLS;
@@ -477,8 +559,8 @@ __device__ __forceinline__ void band_role(const DevPtrs &P, int wg, int nwg, int
 template <int ST, bool COLLIDE, bool ONE_BOX>
 __global__ void __launch_bounds__(256)
     k_band(DevPtrs P, int parity, int full_u, float scale, float inv, int xcd, int nt) {
-    __shared__ int hits[4][64 * GATHER_GROUP];
-    band_role<ST, COLLIDE, ONE_BOX>(P, blockIdx.x, gridDim.x, parity, full_u, scale, inv, xcd, nt, hits);
+    __shared__ int hits[4][64];
+    band_role<ST, COLLIDE, ONE_BOX, 1>(P, blockIdx.x, gridDim.x, parity, full_u, scale, inv, xcd, nt, hits);
 }
 
 // ---------------------------------------------------------------- launchers

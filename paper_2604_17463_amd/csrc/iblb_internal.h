@@ -214,6 +214,7 @@ struct DevPtrs {
     int32_t contrast;           // some box has tau_in set
     int32_t penalty;            // some droplet has a volume penalty
     int32_t moving;             // some box has a moving wall
+    int32_t mesh_lds;           // least LDS (bytes) of a workgroup of the mesh kernels beside the bulk kernel
     int32_t mask_words;         // largest nzw*ny*nx over those boxes
     int32_t pad_rows;           // some row group runs into its row's padding (x1 > nx)
 };

@@ -7,11 +7,21 @@
 
 namespace iblb {
 
+// LDS of the roles, sized at launch.  (Static LDS that allows few workgroups
+// per compute unit makes the compiler claim VGPRs up to the count that allows
+// no more waves than those: 97 instead of 80 for the move kernel, 169 instead
+// of 112 for the node kernel, which then wait longer for room beside the bulk
+// kernel's waves.)
+extern __shared__ __align__(16) char lds[];
+
+// LDS of a mesh launch: what the work needs, or more where the context holds
+// the mesh kernels to fewer workgroups per compute unit (DevPtrs::mesh_lds).
+static size_t lds_bytes(const DevPtrs &P, size_t need) { return need > (size_t)P.mesh_lds ? need : (size_t)P.mesh_lds; }
+
 // Workgroups past the node blocks (with a viscosity contrast) clear this
 // step's inside bits, which the next launch of the chain toggles.
 template <typename R, int MODE>
 __global__ void __launch_bounds__(256) k_move(DevPtrs P, int parity, double *Uout) {
-    __shared__ __align__(16) char lds[MOVE_LDS];
     const int w = blockIdx.x;
     if (w >= P.nblk) {
         mask_clear_role(P, w - P.nblk, gridDim.x - P.nblk, parity);
@@ -25,7 +35,6 @@ __global__ void __launch_bounds__(256) k_move(DevPtrs P, int parity, double *Uou
 // tiles.
 template <typename R, bool NODE, bool FEW, bool CONTRAST>
 __global__ void __launch_bounds__(256) k_aux(DevPtrs P, int parity, int adv) {
-    __shared__ __align__(16) char lds[NODE ? sizeof(NodeLds<R, FEW>) : 256 * 8];
     const int n0 = NODE ? P.nblk : P.n_chunks, n1 = CONTRAST ? P.n_chunks : 0;
     const int w = blockIdx.x;
     if (w < n0) {
@@ -38,9 +47,10 @@ __global__ void __launch_bounds__(256) k_aux(DevPtrs P, int parity, int adv) {
     }
 }
 
+// Many blocks: the kernel runs beside the bulk kernel, whose waves (92
+// VGPRs in FP32) leave room for one of at most 96 where one of them ends.
 template <typename R, bool FEW, bool SPREAD>
 __global__ void __launch_bounds__(256) k_node(DevPtrs P) {
-    __shared__ __align__(16) char lds[sizeof(NodeLds<R, FEW>)];
     node_role<R, FEW, SPREAD>(P, xcd_item(blockIdx.x, gridDim.x), lds);
 }
 
@@ -81,11 +91,11 @@ template <typename R>
 static hipError_t launch_move_t(const DevPtrs &P, int mode, int parity, double *Uout, hipStream_t s) {
     const dim3 block(256), grid(P.nblk), step(P.nblk + mask_clear_groups(P));
     switch (mode) {
-    case MOVE_STEP: hipLaunchKernelGGL((k_move<R, MOVE_STEP>), step, block, 0, s, P, parity, Uout); break;
-    case MOVE_PLACE: hipLaunchKernelGGL((k_move<R, MOVE_PLACE>), step, block, 0, s, P, parity, Uout); break;
-    case MOVE_FLUSH: hipLaunchKernelGGL((k_move<R, MOVE_FLUSH>), grid, block, 0, s, P, parity, Uout); break;
+    case MOVE_STEP: hipLaunchKernelGGL((k_move<R, MOVE_STEP>), step, block, lds_bytes(P, MOVE_LDS), s, P, parity, Uout); break;
+    case MOVE_PLACE: hipLaunchKernelGGL((k_move<R, MOVE_PLACE>), step, block, lds_bytes(P, 0), s, P, parity, Uout); break;
+    case MOVE_FLUSH: hipLaunchKernelGGL((k_move<R, MOVE_FLUSH>), grid, block, MOVE_LDS, s, P, parity, Uout); break;
     case MOVE_BINS: hipLaunchKernelGGL((k_move<R, MOVE_BINS>), grid, block, 0, s, P, parity, Uout); break;
-    case MOVE_U: hipLaunchKernelGGL((k_move<R, MOVE_U>), grid, block, 0, s, P, parity, Uout); break;
+    case MOVE_U: hipLaunchKernelGGL((k_move<R, MOVE_U>), grid, block, MOVE_LDS, s, P, parity, Uout); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -99,9 +109,10 @@ hipError_t launch_move(const DevPtrs &P, bool f64, int mode, int parity, double 
 template <typename R, bool CONTRAST>
 static hipError_t launch_aux_t(const DevPtrs &P, int parity, int adv, hipStream_t s) {
     const dim3 grid((P.penalty ? P.n_chunks : P.nblk) + (CONTRAST ? P.n_chunks : 0) + compact_groups(P)), block(256);
-    if (P.penalty) hipLaunchKernelGGL((k_aux<R, false, false, CONTRAST>), grid, block, 0, s, P, parity, adv);
-    else if (few_blocks(P)) hipLaunchKernelGGL((k_aux<R, true, true, CONTRAST>), grid, block, 0, s, P, parity, adv);
-    else hipLaunchKernelGGL((k_aux<R, true, false, CONTRAST>), grid, block, 0, s, P, parity, adv);
+    if (P.penalty) hipLaunchKernelGGL((k_aux<R, false, false, CONTRAST>), grid, block, lds_bytes(P, 256 * 8), s, P, parity, adv);
+    else if (few_blocks(P)) hipLaunchKernelGGL((k_aux<R, true, true, CONTRAST>), grid, block, sizeof(NodeLds<R, true>), s, P, parity, adv);
+    else hipLaunchKernelGGL((k_aux<R, true, false, CONTRAST>), grid, block, lds_bytes(P, sizeof(NodeLds<R, false>)), s, P,
+                            parity, adv);
     return hipGetLastError();
 }
 
@@ -114,9 +125,10 @@ hipError_t launch_aux(const DevPtrs &P, bool f64, int parity, int adv, hipStream
 template <typename R>
 static hipError_t launch_node_t(const DevPtrs &P, bool spread, hipStream_t s) {
     const dim3 grid(P.nblk), block(256);
-    if (!spread) hipLaunchKernelGGL((k_node<R, false, false>), grid, block, 0, s, P);
-    else if (few_blocks(P)) hipLaunchKernelGGL((k_node<R, true, true>), grid, block, 0, s, P);
-    else hipLaunchKernelGGL((k_node<R, false, true>), grid, block, 0, s, P);
+    if (!spread) hipLaunchKernelGGL((k_node<R, false, false>), grid, block, sizeof(NodeLds<R, false>), s, P);
+    else if (few_blocks(P)) hipLaunchKernelGGL((k_node<R, true, true>), grid, block, sizeof(NodeLds<R, true>), s, P);
+    else hipLaunchKernelGGL((k_node<R, false, true>), grid, block,
+                            lds_bytes(P, sizeof(NodeLds<R, false>)), s, P);
     return hipGetLastError();
 }
 

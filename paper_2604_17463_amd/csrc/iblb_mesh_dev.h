@@ -602,7 +602,7 @@ __device__ __forceinline__ void node_role(const DevPtrs &P, int blk, char *lds) 
             // batches of incident triangles: every load of a batch is issued
             // (entries past the degree read the last one and are not added)
             // before the first is used
-            constexpr int GB = sizeof(R) == 4 ? 6 : 3;
+            constexpr int GB = (FEW ? 6 : 4) / (sizeof(R) == 4 ? 1 : 2);
             const int e0 = P.csr_off[j], e1 = P.csr_off[j + 1];
             for (int e = e0; e < e1; e += GB) {
                 int2 nb[GB];
