@@ -436,6 +436,7 @@ struct iblb_ctx {
     char *scratch = nullptr;  // this device's fixed scratch (iblb_step_static)
     DevPtrs P{};
     Launch L{};
+    bool one_queue = false;  // the steps run as a line of fused launches (uses_one_queue)
     hipGraphExec_t exec[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // [parity][advect first]
     // MULTI_LEN[i] consecutive steps from a pending advection, by starting
     // parity: one launch instead of MULTI_LEN[i] (the host cost of a launch
@@ -484,13 +485,31 @@ Launch default_launch(const iblb_ctx *c) {
         pop_bytes += 2 * (size_t)Q * H.plane * elem_bytes(c->plan.storage);
     }
     Launch L{};
-    L.bx = nxmax <= 32 ? 32 : (nxmax <= 64 ? 64 : (nxmax <= 128 ? 128 : 256));
+    // (32 threads along x only without droplets: the one-queue step's waves
+    // lie in one row each)
+    L.bx = nxmax <= 32 && c->plan.nblk == 0 ? 32 : (nxmax <= 64 ? 64 : (nxmax <= 128 ? 128 : 256));
     L.by = 256 / L.bx;
     // streaming stores once both population buffers exceed the 256 MiB
     // last-level cache
     L.nt = pop_bytes > ((size_t)256 << 20) ? 1 : 0;
     L.cpt = 1;
     return L;
+}
+
+// Whether the steps run as a line of fused launches on the caller's queue
+// (launch_fused, with the times on both sides of the line) instead of the
+// bulk kernel and the mesh chain on two: with the default launch, few node
+// blocks, and both population buffers together at most 100 MiB; 32 MiB with a
+// viscosity contrast, where the rows wait for the inside bits (32x32x24 32.2
+// -> 24.1 us per step, 64x64x64 (40 MB) 44.2 and 43.2, 96x96x96 47.5 and 54.2).
+bool one_queue_size(const iblb_ctx *c) {
+    size_t pop_bytes = 0;
+    for (const BoxHost &H : c->plan.boxes) pop_bytes += 2 * (size_t)Q * H.plane * elem_bytes(c->plan.storage);
+    return c->plan.nblk > 0 && c->plan.nblk <= c->P.n_cus && pop_bytes <= (size_t)(c->P.contrast ? 32 : 100) << 20;
+}
+bool uses_one_queue(const iblb_ctx *c) {
+    const Launch D = default_launch(c), &L = c->L;
+    return one_queue_size(c) && L.bx == D.bx && L.by == D.by && L.nt == D.nt && L.cpt == 1 && L.maxg == 0 && L.after == 0;
 }
 
 // Least LDS of a workgroup of the mesh kernels, which holds them to one (more
@@ -520,6 +539,7 @@ int mesh_lds(const iblb_ctx *c) {
 // against 5.69 TB/s for the stream-collide of a 512x512x256 box, 5.31
 // against 5.67 at 1024 cells per row).
 iblb_status upload_rows(iblb_ctx *c) {
+    c->one_queue = uses_one_queue(c);
     std::vector<RowGroup> rows;
     const int R = c->L.by * c->L.cpt, BX = c->L.bx;
     for (int b = 0; b < (int)c->plan.boxes.size(); ++b) {
@@ -587,6 +607,36 @@ iblb_status enqueue_chain(iblb_ctx *c, const DevPtrs &P, int p, bool advect, hip
     return IBLB_OK;
 }
 
+// The one-queue form of enqueue_steps: the line of fused launches per step.
+iblb_status enqueue_one_queue(iblb_ctx *c, hipStream_t s, int parity, bool advect_first, int n) {
+    const int full_u = (c->plan.flags & IBLB_FLAG_FULL_U) ? 1 : 0, ng = c->P.n_rowgroups;
+    const float scale = (float)c->plan.scale;
+    for (int k = 0; k < n; ++k) {
+        const int p = parity ^ (k & 1), adv = (advect_first || k > 0) ? 1 : 0;
+        // shares of the row groups, in hundredths, beside the move, node and
+        // band work (128x128x64 in FP16: 42.2 us per step, with 35/30/35 44.6,
+        // with 50/5/45 43.2)
+        int share[3] = {45, 15, 40};
+        if (!adv || c->P.contrast) share[0] = 0;
+        if (c->P.contrast && !c->P.penalty) share[1] = 0;  // the inside bits come with the forces
+        const int64_t sum = share[0] + share[1] + share[2];
+        const int r1 = (int)(ng * share[2] / sum), r2 = (int)(ng * (share[2] + share[1]) / sum);
+        auto go = [&](int phase, int r0, int rows) {
+            return launch_fused(c->P, c->plan.storage, phase, p, adv, full_u, scale, c->L, r0, rows, s);
+        };
+        if (adv) HIPCHK(c, go(PH_MOVE, r2, ng - r2));
+        else HIPCHK(c, launch_move(c->P, is_f64(c), MOVE_PLACE, p, nullptr, s));
+        if (c->P.penalty) {
+            HIPCHK(c, launch_aux(c->P, is_f64(c), p, adv, s));
+            HIPCHK(c, go(PH_NODE, r1, r2 - r1));
+        } else {
+            HIPCHK(c, go(PH_AUX_NODE, r1, r2 - r1));
+        }
+        HIPCHK(c, go(PH_BAND, 0, r1));
+    }
+    return IBLB_OK;
+}
+
 // n consecutive time steps on stream s, the first with buffer parity
 // `parity`.  Per step, on the second stream, the mesh chain: advection of
 // the previous step's nodes and tile stamps -> volumes, inside bits, list of
@@ -617,6 +667,7 @@ iblb_status enqueue_steps(iblb_ctx *c, hipStream_t s, int parity, bool advect_fi
             HIPCHK(c, launch_bulk(c->P, c->plan.storage, parity ^ (k & 1), full_u, scale, c->L, false, s));
         return IBLB_OK;
     }
+    if (c->one_queue) return enqueue_one_queue(c, s, parity, advect_first, n);
     if (c->L.after) {
         for (int k = 0; k < n; ++k) {
             const int p = parity ^ (k & 1);
@@ -877,6 +928,14 @@ iblb_status autotune(iblb_ctx *c) {
         const int cus = c->P.n_cus;
         double sbest = 1e300;
         Launch chosen = best;
+        if (one_queue_size(c)) {
+            c->L = chosen = default_launch(c);
+            iblb_status st = upload_rows(c);
+            if (st == IBLB_OK) st = reset_state(c);
+            if (st == IBLB_OK) st = build_graphs(c);
+            if (st == IBLB_OK) st = time_steps(c, &sbest);
+            if (st != IBLB_OK) return st;
+        }
         for (size_t si = 0; si < shapes.size(); ++si) {
             const Launch &shape = shapes[si];
             const int wpg = shape.bx * shape.by / 64;  // waves per workgroup
@@ -908,6 +967,8 @@ iblb_status autotune(iblb_ctx *c) {
         best = chosen;
         iblb_status st = reset_state(c);
         if (st != IBLB_OK) return st;
+    } else if (one_queue_size(c)) {
+        best = default_launch(c);  // eager steps: the one-queue line without timing
     }
     c->L = best;
     iblb_status st = upload_rows(c);

@@ -191,6 +191,7 @@ __global__ void __launch_bounds__(K1_MAX_THREADS)
 // 128x128x64 51 against 49 us; 250x250x150 (band kernel 65 -> 262 us).
 // Against tests that loaded each bound behind the one before it, the band
 // kernel of 160 blocks alone went from 14.2 to 11.8 us.
+constexpr int SCAN_GROUPS = SCAN_GROUP / 64;
 constexpr int GATHER_BATCH = 4;
 
 template <typename R, int GROUP>
@@ -563,6 +564,88 @@ __global__ void __launch_bounds__(256)
     band_role<ST, COLLIDE, ONE_BOX, 1>(P, blockIdx.x, gridDim.x, parity, full_u, scale, inv, xcd, nt, hits);
 }
 
+// ------------------------------------------------------- one-queue step
+// A small step is the latency of its chain: move, volumes and tile list, node
+// forces, band tiles, each launch waiting for the one before.  On two queues
+// the bulk kernel runs beside them, but each dependency between the queues
+// costs about 10 us, two of them in a step.  Here a step is a line of launches
+// on one queue, and the bulk rows go along in the last workgroups of three:
+//   PH_MOVE      advection, stamps, records, cleared inside bits | rows, every cell
+//   (the volumes and the list alone: launch_aux)
+//   PH_NODE      forces and partial spread                       | rows, without the band tiles
+//   PH_BAND      band tiles                                      | rows, without the band tiles
+// and, when no droplet has a volume penalty, PH_AUX_NODE (inside bits, list
+// and forces) in the place of launch_aux and PH_NODE.  The rows beside
+// PH_MOVE are computed before the stamps are known; their band cells are
+// overwritten by PH_BAND.  With a viscosity contrast rows can only follow the
+// inside bits.
+//
+// Measured per step against the two queues: 32x32x24 with 642 nodes FP32 31.2
+// -> 23.4 us, FP64 43.6 -> 35.0; 45x37x41 39.2 -> 31.0; 64x48x40 with 2,562
+// nodes 32.9 -> 28.4; 96x96x64 with 10,242 nodes 44.6 -> 41.2; 128x128x64 in
+// FP16 44.2 -> 42.2, in FP32 49.6 -> 50.4; 160x160x64 64 -> 76: larger boxes
+// fill the chip with rows in every launch, and each launch ends with its own
+// tail.
+struct FusedGrid {
+    int n0, n1, n2;  // workgroups of the phase's three kinds of mesh work
+    int r0, bxs;     // first row group; log2 of the threads along x (64 to 256)
+};
+
+// LDS of a phase's mesh work, sized at launch (static LDS would claim VGPRs).
+template <typename R, int PHASE>
+constexpr int fused_lds = PHASE == PH_MOVE     ? MOVE_LDS
+                                          : PHASE == PH_BAND   ? (int)sizeof(int[4][64 * SCAN_GROUPS])
+                                               : (int)sizeof(NodeLds<R, true>);
+extern __shared__ __align__(16) char lds[];
+
+template <int ST, bool EXT, int PHASE>
+__global__ void __launch_bounds__(256, ST == 0 ? 1 : 4)
+    k_fused(DevPtrs P, int parity, int adv, int full_u, float scale, float inv, int nt, FusedGrid G) {
+    using R = typename Stor<ST>::R;
+    int w = blockIdx.x;
+    if (w < G.n0) {
+        if constexpr (PHASE == PH_MOVE)
+            move_role<R, MOVE_STEP>(P, xcd_item(w, G.n0), w == 0, parity, 1, nullptr, lds);
+        else if constexpr (PHASE == PH_BAND) {
+            auto hits = (int(*)[64 * SCAN_GROUPS])lds;
+            if (P.n_boxes == 1) band_role<ST, true, true, SCAN_GROUPS>(P, w, G.n0, parity, full_u, scale, inv, 0, nt, hits);
+            else band_role<ST, true, false, SCAN_GROUPS>(P, w, G.n0, parity, full_u, scale, inv, 0, nt, hits);
+        } else
+            node_role<R, true, true>(P, xcd_item(w, G.n0), lds);
+        return;
+    }
+    w -= G.n0;
+    if constexpr (PHASE == PH_MOVE) {
+        if (w < G.n1) {
+            mask_clear_role(P, w, G.n1, parity);
+            return;
+        }
+        w -= G.n1;
+    }
+    if constexpr (PHASE == PH_AUX_NODE) {
+        if constexpr (EXT) {  // n1 is 0 without a contrast
+            if (w < G.n1) {
+                inside_role<R>(P, w, parity);
+                return;
+            }
+            w -= G.n1;
+        }
+        if (w < G.n2) {
+            compact_role(P, w, parity, *P.ctr + adv);
+            return;
+        }
+        w -= G.n2;
+    }
+    constexpr bool SKIP = PHASE != PH_MOVE;
+    const int epoch = PHASE == PH_MOVE       ? -2
+                      : PHASE == PH_AUX_NODE ? *P.ctr + adv
+                                             : P.step_epoch[parity];
+    const IBLB_CONST RowGroup *rows = (const IBLB_CONST RowGroup *)P.rows;
+    const int BX = 1 << G.bxs;
+    bulk_rows<ST, true, 2, 1, EXT, SKIP, true>(P, rows[G.r0 + w], threadIdx.x & (BX - 1), threadIdx.x >> G.bxs, BX,
+                                               256 >> G.bxs, parity, epoch, full_u, scale, inv, nt);
+}
+
 // ---------------------------------------------------------------- launchers
 template <int ST, bool UROW, bool NT, bool SKIP, bool PADW>
 static void launch_bulk_p(const DevPtrs &P, int parity, int full_u, float scale, float inv, const Launch &L,
@@ -634,6 +717,15 @@ hipError_t launch_bulk(const DevPtrs &P, int storage, int parity, int full_u, fl
 // Workgroups of the band kernel (four waves, one tile each at a time; a
 // wave loops over what is left of the list).
 static int band_groups(const DevPtrs &P) { return std::min((P.total_tiles + 3) / 4, BAND_GRID); }
+// The same in the one-queue step, where empty workgroups would delay the
+// bulk rows behind them (128x128x64 with 160 node blocks: 4,096 workgroups 54
+// us per step, 640 50 us): four per node block, as a block of 64 nodes about
+// one cell apart covers 13 to 16 tiles, and more where few coarse blocks
+// cover more (45x37x41 with 11 blocks: 44 workgroups 34 us, 176 31 us).
+static int fused_band_groups(const DevPtrs &P) {
+    return std::max(1, std::min((P.total_tiles + 3) / 4, std::min(std::max(4 * P.nblk, std::min(16 * P.nblk, 256)), BAND_GRID)));
+}
+
 template <int ST, bool C>
 static void launch_band_t(const DevPtrs &P, int parity, int full_u, float scale, int nt, hipStream_t s) {
     // one wave per tile up to 32,768 waves (workgroups of four); large
@@ -667,6 +759,57 @@ hipError_t launch_band(const DevPtrs &P, int storage, int parity, int full_u, fl
         launch_band_t<1, false>(P, parity, full_u, scale, 0, s);
     }
     return hipGetLastError();
+}
+
+template <int ST, int PHASE>
+static hipError_t launch_fused_p(const DevPtrs &P, int parity, int adv, int full_u, float scale, const Launch &L, int r0,
+                                 int nrows, hipStream_t s) {
+    FusedGrid G{0, 0, 0, r0, 0};
+    while ((1 << G.bxs) < L.bx) ++G.bxs;
+    // never launch a shape the kernel was not written for
+    if ((1 << G.bxs) != L.bx || L.bx < 64 || L.bx * L.by != 256 || L.cpt != 1 || r0 < 0 || nrows < 0 ||
+        r0 + nrows > P.n_rowgroups || !few_blocks(P) || (P.contrast && nrows > 0 && PHASE != PH_NODE && PHASE != PH_BAND))
+        return hipErrorInvalidValue;
+    if (PHASE == PH_MOVE) {
+        G.n0 = P.nblk;
+        G.n1 = mask_clear_groups(P);
+    } else if (PHASE == PH_AUX_NODE) {
+        G.n0 = P.nblk;
+        G.n1 = P.contrast ? P.n_chunks : 0;
+        G.n2 = compact_groups(P);
+    } else {
+        G.n0 = PHASE == PH_NODE ? P.nblk : fused_band_groups(P);
+    }
+    const dim3 grid(G.n0 + G.n1 + G.n2 + nrows), block(256);
+    const float inv = 1.0f / scale;
+    const size_t bytes = fused_lds<typename Stor<ST>::R, PHASE>;
+    if (P.contrast || P.moving)
+        hipLaunchKernelGGL((k_fused<ST, true, PHASE>), grid, block, bytes, s, P, parity, adv, full_u, scale, inv, L.nt, G);
+    else
+        hipLaunchKernelGGL((k_fused<ST, false, PHASE>), grid, block, bytes, s, P, parity, adv, full_u, scale, inv, L.nt, G);
+    return hipGetLastError();
+}
+
+template <int ST>
+static hipError_t launch_fused_s(const DevPtrs &P, int phase, int parity, int adv, int full_u, float scale,
+                                 const Launch &L, int r0, int nrows, hipStream_t s) {
+    switch (phase) {
+    case PH_MOVE: return launch_fused_p<ST, PH_MOVE>(P, parity, adv, full_u, scale, L, r0, nrows, s);
+    case PH_NODE: return launch_fused_p<ST, PH_NODE>(P, parity, adv, full_u, scale, L, r0, nrows, s);
+    case PH_BAND: return launch_fused_p<ST, PH_BAND>(P, parity, adv, full_u, scale, L, r0, nrows, s);
+    case PH_AUX_NODE: return launch_fused_p<ST, PH_AUX_NODE>(P, parity, adv, full_u, scale, L, r0, nrows, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_fused(const DevPtrs &P, int storage, int phase, int parity, int adv, int full_u, float scale,
+                        const Launch &L, int r0, int nrows, hipStream_t s) {
+    switch (storage) {
+    case 0: return launch_fused_s<0>(P, phase, parity, adv, full_u, scale, L, r0, nrows, s);
+    case 1: return launch_fused_s<1>(P, phase, parity, adv, full_u, scale, L, r0, nrows, s);
+    case 2: return launch_fused_s<2>(P, phase, parity, adv, full_u, scale, L, r0, nrows, s);
+    default: return launch_fused_s<3>(P, phase, parity, adv, full_u, scale, L, r0, nrows, s);
+    }
 }
 
 }  // namespace iblb

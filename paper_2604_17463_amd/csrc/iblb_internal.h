@@ -263,6 +263,11 @@ hipError_t launch_bulk(const DevPtrs &P, int storage, int parity, int full_u, fl
                        const Launch &L, bool skip_band, hipStream_t s);
 hipError_t launch_band(const DevPtrs &P, int storage, int parity, int full_u, float scale,
                        bool collide, int nt, hipStream_t s);
+// One launch of the one-queue step (iblb_fluid.hip): the mesh work of
+// `phase` and the bulk row groups [r0, r0 + nrows) beside it.
+enum { PH_MOVE, PH_NODE, PH_BAND, PH_AUX_NODE };
+hipError_t launch_fused(const DevPtrs &P, int storage, int phase, int parity, int adv, int full_u, float scale,
+                        const Launch &L, int r0, int nrows, hipStream_t s);
 hipError_t launch_epoch(const DevPtrs &P, hipStream_t s);
 hipError_t launch_inside(const DevPtrs &P, bool f64, int slot, hipStream_t s);
 hipError_t launch_mask_clear(const DevPtrs &P, int slot, hipStream_t s);
