@@ -678,7 +678,7 @@ iblb_status enqueue_steps(iblb_ctx *c, hipStream_t s, int parity, bool advect_fi
             HIPCHK(c, hipEventRecord(c->ev_chain, c->ib));
             HIPCHK(c, launch_bulk(c->P, c->plan.storage, p, full_u, scale, c->L, false, s));
             HIPCHK(c, hipStreamWaitEvent(s, c->ev_chain, 0));
-            HIPCHK(c, launch_band(c->P, c->plan.storage, p, full_u, scale, true, c->L.nt, s));
+            HIPCHK(c, launch_band(c->P, c->plan.storage, p, full_u, scale, true, c->L.nt, false, s));
         }
         return IBLB_OK;
     }
@@ -691,7 +691,7 @@ iblb_status enqueue_steps(iblb_ctx *c, hipStream_t s, int parity, bool advect_fi
         HIPCHK(c, hipStreamWaitEvent(s, c->ev_chain, 0));
         HIPCHK(c, launch_bulk(c->P, c->plan.storage, p, full_u, scale, c->L, true, s));
         if (k > 0) HIPCHK(c, hipStreamWaitEvent(c->ib, c->ev_bulk, 0));  // the previous step's bulk kernel
-        HIPCHK(c, launch_band(c->P, c->plan.storage, p, full_u, scale, true, c->L.nt, c->ib));
+        HIPCHK(c, launch_band(c->P, c->plan.storage, p, full_u, scale, true, c->L.nt, true, c->ib));
         HIPCHK(c, hipEventRecord(c->ev_bulk, s));
     }
     HIPCHK(c, hipEventRecord(c->ev_join, c->ib));
@@ -1517,7 +1517,7 @@ iblb_status iblb_step_static(iblb_ctx *c, int64_t n) {
         const iblb_status st = enqueue_chain(c, V, par, k > 0, s, nullptr);
         if (st != IBLB_OK) return st;
         if (k > 0) ++c->epoch;  // the advection starts the next epoch
-        HIPCHK(c, launch_band(V, p.storage, par, full_u, scale, true, c->L.nt, s));
+        HIPCHK(c, launch_band(V, p.storage, par, full_u, scale, true, c->L.nt, false, s));
         HIPCHK(c, launch_bulk(V, p.storage, par, full_u, scale, c->L, true, s));
         c->last_step_epoch = c->epoch;
         c->last_step_parity = par;
@@ -1785,7 +1785,7 @@ iblb_status iblb_compute_spread(iblb_ctx *c, int32_t b, double *F_out, uint8_t *
         const iblb_status st = enqueue_chain(c, c->P, c->parity, false, c->stream, nullptr);
         if (st != IBLB_OK) return st;
     }
-    HIPCHK(c, launch_band(c->P, c->plan.storage, c->parity, 0, (float)c->plan.scale, false, 0, c->stream));
+    HIPCHK(c, launch_band(c->P, c->plan.storage, c->parity, 0, (float)c->plan.scale, false, 0, false, c->stream));
     HIPCHK(c, launch_epoch(c->P, c->stream));
     const int32_t used = c->epoch;
     ++c->epoch;

@@ -715,22 +715,29 @@ hipError_t launch_bulk(const DevPtrs &P, int storage, int parity, int full_u, fl
 }
 
 // Workgroups of the band kernel (four waves, one tile each at a time; a
-// wave loops over what is left of the list).
+// wave loops over what is left of the list) when it has the chip to itself:
+// the list's length is not known here, so one wave for each tile there can
+// be, up to 32,768 waves; most find nothing and end.
 static int band_groups(const DevPtrs &P) { return std::min((P.total_tiles + 3) / 4, BAND_GRID); }
-// The same in the one-queue step, where empty workgroups would delay the
-// bulk rows behind them (128x128x64 with 160 node blocks: 4,096 workgroups 54
-// us per step, 640 50 us): four per node block, as a block of 64 nodes about
-// one cell apart covers 13 to 16 tiles, and more where few coarse blocks
-// cover more (45x37x41 with 11 blocks: 44 workgroups 34 us, 176 31 us).
-static int fused_band_groups(const DevPtrs &P) {
-    return std::max(1, std::min((P.total_tiles + 3) / 4, std::min(std::max(4 * P.nblk, std::min(16 * P.nblk, 256)), BAND_GRID)));
+// The same beside the bulk kernel (per = 1) or in the one-queue step (per =
+// 4), where empty workgroups take dispatch and room from the bulk rows: `per`
+// for each node block, as a block of 64 nodes about one cell apart covers 13
+// to 16 tiles, and more where few coarse blocks cover more (45x37x41 with 11
+// blocks: 44 workgroups 34 us per step, 176 31 us).  In one queue the band's
+// tiles start first and nothing follows them, so each wave gets about one
+// (128x128x64 with 160 node blocks: 4,096 workgroups 54 us per step, 640 50
+// us).  Beside the bulk kernel, which takes longer, a wave takes about four
+// one after another; per step with up to 8,192 workgroups and with one per
+// node block: 250x250x150 FP32 303.6 and 300.3 us, 256x256x128 BF16 183.7
+// and 180.5, 128x96x192 FP32 with a contrast 81.3 and 79.8, 64 boxes of
+// 128x128x64 1,037 and 1,022, 512x512x256 with 27 droplets 1,893 and 1,889.
+static int shared_band_groups(const DevPtrs &P, int per) {
+    return std::max(1, std::min((P.total_tiles + 3) / 4, std::min(std::max(per * P.nblk, std::min(16 * P.nblk, 256)), BAND_GRID)));
 }
 
 template <int ST, bool C>
-static void launch_band_t(const DevPtrs &P, int parity, int full_u, float scale, int nt, hipStream_t s) {
-    // one wave per tile up to 32,768 waves (workgroups of four); large
-    // bands (many boxes or droplets) loop over the rest of the list
-    const int grid = band_groups(P);
+static void launch_band_t(const DevPtrs &P, int parity, int full_u, float scale, int nt, bool shared, hipStream_t s) {
+    const int grid = shared ? shared_band_groups(P, 1) : band_groups(P);
     // a full grid (a multiple of eight workgroups) takes the list in XCD
     // ranges; a small one keeps the interleaved order, whose first entry
     // loads beside the list count (latency decides there)
@@ -744,19 +751,19 @@ static void launch_band_t(const DevPtrs &P, int parity, int full_u, float scale,
 }
 
 hipError_t launch_band(const DevPtrs &P, int storage, int parity, int full_u, float scale, bool collide,
-                       int nt, hipStream_t s) {
+                       int nt, bool shared, hipStream_t s) {
     if (P.nblk == 0 || P.total_tiles == 0) return hipSuccess;
     if (collide) {
         switch (storage) {
-        case 0: launch_band_t<0, true>(P, parity, full_u, scale, nt, s); break;
-        case 1: launch_band_t<1, true>(P, parity, full_u, scale, nt, s); break;
-        case 2: launch_band_t<2, true>(P, parity, full_u, scale, nt, s); break;
-        default: launch_band_t<3, true>(P, parity, full_u, scale, nt, s); break;
+        case 0: launch_band_t<0, true>(P, parity, full_u, scale, nt, shared, s); break;
+        case 1: launch_band_t<1, true>(P, parity, full_u, scale, nt, shared, s); break;
+        case 2: launch_band_t<2, true>(P, parity, full_u, scale, nt, shared, s); break;
+        default: launch_band_t<3, true>(P, parity, full_u, scale, nt, shared, s); break;
         }
     } else if (storage == 0) {
-        launch_band_t<0, false>(P, parity, full_u, scale, 0, s);
+        launch_band_t<0, false>(P, parity, full_u, scale, 0, shared, s);
     } else {
-        launch_band_t<1, false>(P, parity, full_u, scale, 0, s);
+        launch_band_t<1, false>(P, parity, full_u, scale, 0, shared, s);
     }
     return hipGetLastError();
 }
@@ -778,7 +785,7 @@ static hipError_t launch_fused_p(const DevPtrs &P, int parity, int adv, int full
         G.n1 = P.contrast ? P.n_chunks : 0;
         G.n2 = compact_groups(P);
     } else {
-        G.n0 = PHASE == PH_NODE ? P.nblk : fused_band_groups(P);
+        G.n0 = PHASE == PH_NODE ? P.nblk : shared_band_groups(P, 4);
     }
     const dim3 grid(G.n0 + G.n1 + G.n2 + nrows), block(256);
     const float inv = 1.0f / scale;

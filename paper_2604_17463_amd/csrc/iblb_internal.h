@@ -261,8 +261,9 @@ hipError_t launch_volume(const DevPtrs &P, bool f64, hipStream_t s);
 hipError_t launch_set_v0(const DevPtrs &P, hipStream_t s);
 hipError_t launch_bulk(const DevPtrs &P, int storage, int parity, int full_u, float scale,
                        const Launch &L, bool skip_band, hipStream_t s);
+// shared: the bulk kernel runs beside it (a smaller grid then).
 hipError_t launch_band(const DevPtrs &P, int storage, int parity, int full_u, float scale,
-                       bool collide, int nt, hipStream_t s);
+                       bool collide, int nt, bool shared, hipStream_t s);
 // One launch of the one-queue step (iblb_fluid.hip): the mesh work of
 // `phase` and the bulk row groups [r0, r0 + nrows) beside it.
 enum { PH_MOVE, PH_NODE, PH_BAND, PH_AUX_NODE };
