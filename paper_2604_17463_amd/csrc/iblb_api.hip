@@ -517,12 +517,12 @@ bool uses_one_queue(const iblb_ctx *c) {
 // beside the bulk kernel.  Their waves mostly wait for memory, each in the
 // place of a bulk wave that would keep more of it in flight: as long as the
 // chain ends before the bulk kernel does, fewer at a time cost nothing.  One
-// per compute unit against no limit: 250x250x150 with 927 node blocks 300
-// against 311 us per step, 512x512x256 with 2,576 blocks 1,891 against 1,906;
-// but 64 boxes with 5,837 blocks on 28 M cells 1,053 against 1,052 us, and two
-// per compute unit 1,027: there one leaves the chain (about 40 us per 256
-// blocks) longer than the bulk kernel.  At most 256 blocks are one round in
-// any case and keep their latency.
+// and two per compute unit, and no limit: 250x250x150 with 927 node blocks
+// 293, 301 and 308 us per step, 512x512x256 with 2,576 blocks 1,857, 1,874 and
+// 1,894; but 64 boxes with 5,837 blocks on 28 M cells 986, 967 and 1,018 us and
+// 256x256x128 BF16 with 641 blocks 177, 160 and 167: there one leaves the chain
+// (about 40 us per 256 blocks) longer than the bulk kernel.  At most 256 blocks
+// are one round in any case and keep their latency.
 int mesh_lds(const iblb_ctx *c) {
     if (c->plan.nblk <= 256) return 0;
     double bulk_us = 0;

@@ -337,13 +337,13 @@ __device__ __forceinline__ void collide(const typename Stor<ST>::R (&g)[Q], type
 
 // Store the 19 post-collision values at byte offset `own` of each plane.
 template <int ST, bool NT>
-__device__ __forceinline__ void store_ptr(IBLB_GLOBAL char *__restrict__ dst, uint64_t pb, uint32_t own,
+__device__ __forceinline__ void store_ptr(IBLB_GLOBAL char *__restrict__ dst, uint64_t pb, uint32_t row, uint32_t x,
                                           const typename Stor<ST>::R (&out)[Q]) {
     using S = Stor<ST>;
     using T = typename S::T;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        IBLB_GLOBAL T *p = (IBLB_GLOBAL T *)(dst + (uint64_t)i * pb + own);
+        IBLB_GLOBAL T *p = (IBLB_GLOBAL T *)(dst + (uint64_t)i * pb + row + x);
         if constexpr (NT)
             S::put_nt(p, out[i]);
         else

@@ -35,7 +35,9 @@ __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST Row
     constexpr uint32_t EB = sizeof(typename S::T);
     // 2-byte storage goes through buffer resources (scalar row offsets, one
     // per-lane offset per access); 4- and 8-byte storage measured faster with
-    // plain global addressing
+    // plain global addressing (us per step, buffer and global: 250x250x150
+    // FP32 292 and 290, 64 boxes of 128x128x64 971 and 962, 256x256x128 FP64
+    // 494 and 482)
     constexpr bool BUF = UROW && EB == 2;
     const IBLB_CONST BoxDev *B = (const IBLB_CONST BoxDev *)P.boxes + rg.box;
     const int nx = B->nx, ny = B->ny, nz = B->nz, sx = B->sx;
@@ -50,16 +52,20 @@ __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST Row
     const IBLB_GLOBAL int32_t *stamp = (const IBLB_GLOBAL int32_t *)B->stamp[parity];
     const int tnx = B->tnx, tny = B->tny;
     const bool skip_box = SKIP && B->blk_end > B->blk_begin;  // only boxes holding droplets
-    R kw[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) kw[a] = (R)(6.0 * B->rho0 * (double)scale * B->uw[a]);
     const R gx = (R)B->g[0], gy = (R)B->g[1], gz = (R)B->g[2];
     IBLB_GLOBAL R *__restrict__ uf = (IBLB_GLOBAL R *)B->ufull;
     const uint64_t plane = (uint64_t)B->plane;
     const PopRes rs = pop_res((const void *)src, pb), rd = pop_res((const void *)dst, pb);
     // row r = z * ny + y, stepped by BY without a division per row; a
     // thread takes CPT rows (BY apart) at a time, with the loads of all
-    // of them issued before the first collision
+    // of them issued before the first collision.  UROW: a row group has at
+    // most BY * CPT rows of at most BX cells (padding included), so both
+    // loops are left after one pass: what the compiler moved in front of
+    // them, 38 plane and row addresses above all, outgrew the scalar
+    // registers and was kept in vector lanes (FP32 without padded rows: 533
+    // vector instructions, 198 of them such moves, and 91 VGPRs, now 334, 30
+    // and 53; FP64 528 and 153, now 336 and 91; BF16 423 and 84, now 313 and
+    // 49).
     int r = rg.r0 + ty;
     int z = r / ny, y = r - z * ny;
     for (; r < rg.r1; r += BY * CPT) {
@@ -101,9 +107,13 @@ __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST Row
                 if (skip_box && on[k])
                     mine[k] = stamp[((int64_t)(rzk[k] >> TZS) * tny + (ryk[k] >> TYS)) * tnx + (xs >> TXS)] != epoch;
             }
+            if (CPT == 1 && !mine[0]) {
+                if constexpr (UROW) break;
+                else continue;
+            }
 #pragma unroll
             for (int k = 0; k < CPT; ++k) {
-                if (!mine[k]) continue;
+                if (CPT > 1 && !mine[k]) continue;
                 if constexpr (BUF)
                     pull_buf<ST>(rs, (uint32_t)pb, ra[k], xo, g[k]);
                 else
@@ -111,11 +121,16 @@ __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST Row
             }
 #pragma unroll
             for (int k = 0; k < CPT; ++k) {
-                if (!mine[k]) continue;
+                if (CPT > 1 && !mine[k]) continue;
                 R out[Q], u[3], rho;
-                const uint32_t own = ra[k].ro[1][1] + xst;
+                const uint32_t row = UROW ? __builtin_amdgcn_readfirstlane(ra[k].ro[1][1]) : ra[k].ro[1][1];
                 R om = omega, gu = guo;
-                if (EXT && moving && (ra[k].wlo || ra[k].whi)) wall_shift<R>(g[k], ra[k].wlo, ra[k].whi, kw);
+                if (EXT && moving && (ra[k].wlo || ra[k].whi)) {
+                    R kw[4];
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) kw[a] = (R)(6.0 * B->rho0 * (double)scale * B->uw[a]);
+                    wall_shift<R>(g[k], ra[k].wlo, ra[k].whi, kw);
+                }
                 if (EXT && contrast) {
                     // this step's inside bits (computed by the mesh
                     // chain, which this kernel follows)
@@ -132,18 +147,18 @@ __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST Row
                 }
                 if (NTM == 1 || (NTM == 2 && nt)) {
                     if constexpr (BUF)
-                        store_buf<ST, true>(rd, (uint32_t)pb, ra[k].ro[1][1], xst, out);
+                        store_buf<ST, true>(rd, (uint32_t)pb, row, xst, out);
                     else
-                        store_ptr<ST, true>(dst, pb, own, out);
+                        store_ptr<ST, true>(dst, pb, row, xst, out);
                 } else {
                     if constexpr (BUF)
-                        store_buf<ST, false>(rd, (uint32_t)pb, ra[k].ro[1][1], xst, out);
+                        store_buf<ST, false>(rd, (uint32_t)pb, row, xst, out);
                     else
-                        store_ptr<ST, false>(dst, pb, own, out);
+                        store_ptr<ST, false>(dst, pb, row, xst, out);
                 }
                 if (PADW && pad) continue;
                 if (full_u) {
-                    const uint64_t e = own / EB;
+                    const uint64_t e = (row + xst) / EB;
                     uf[e] = u[0];
                     uf[plane + e] = u[1];
                     uf[2 * plane + e] = u[2];
@@ -151,12 +166,24 @@ __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST Row
                 if (!(rho > R(0) && rho < R(FLT_MAX))) atomicOr(P.status, BIT_RHO);
                 if (u[0] * u[0] + u[1] * u[1] + u[2] * u[2] > R(1) / R(3)) atomicOr(P.status, BIT_MACH);
             }
+            if constexpr (UROW) break;
         }
+        if constexpr (UROW) break;
     }
 }
 
+// Most waves of the bulk kernel per SIMD: where more would fit, their rows
+// come from more places of the population planes at a time and the memory
+// delivers less, and they leave no room for the mesh kernels beside them; with
+// fewer, too little is in flight.  us per step with 3, 4, 5, 6 and 8:
+// 256x256x128 FP64 482, 489, 548, 555, 551; 250x250x150 FP32 314, 294, 291,
+// 324, 355 and 64 boxes of 128x128x64 1,112, 997, 962, 964, 1,076; 256x256x128
+// BF16 211, 184, 173, 157, 174.  (Before the loops above went, FP64 had 3, FP32
+// and BF16 5, at 484, 297, 1,020 and 183 us.)
+constexpr int bulk_waves(int st) { return st == 0 ? 3 : st == 1 ? 5 : 6; }
+
 template <int ST, bool UROW, bool NT, int CPT, bool EXT, bool SKIP, bool PADW>
-__global__ void __launch_bounds__(K1_MAX_THREADS)
+__global__ void __launch_bounds__(K1_MAX_THREADS) __attribute__((amdgpu_waves_per_eu(1, bulk_waves(ST))))
     k_bulk(DevPtrs P, int parity, int full_u, float scale, float inv) {
     const IBLB_CONST RowGroup *rows = (const IBLB_CONST RowGroup *)P.rows;
     // epoch of this step's stamps (written by the mesh chain, which this

@@ -47,8 +47,8 @@ __global__ void __launch_bounds__(256) k_aux(DevPtrs P, int parity, int adv) {
     }
 }
 
-// Many blocks: the kernel runs beside the bulk kernel, whose waves (92
-// VGPRs in FP32) leave room for one of at most 96 where one of them ends.
+// Many blocks: the kernel runs beside the bulk kernel, and its waves take
+// the room that a bulk wave of 80 (16 bits) to 136 VGPRs (FP64) leaves.
 template <typename R, bool FEW, bool SPREAD>
 __global__ void __launch_bounds__(256) k_node(DevPtrs P) {
     node_role<R, FEW, SPREAD>(P, xcd_item(blockIdx.x, gridDim.x), lds);
