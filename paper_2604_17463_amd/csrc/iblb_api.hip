@@ -499,13 +499,19 @@ Launch default_launch(const iblb_ctx *c) {
 // Whether the steps run as a line of fused launches on the caller's queue
 // (launch_fused, with the times on both sides of the line) instead of the
 // bulk kernel and the mesh chain on two: with the default launch, few node
-// blocks, and both population buffers together at most 100 MiB; 32 MiB with a
-// viscosity contrast, where the rows wait for the inside bits (32x32x24 32.2
-// -> 24.1 us per step, 64x64x64 (40 MB) 44.2 and 43.2, 96x96x96 47.5 and 54.2).
+// blocks, at most 1.2 million cells and both population buffers together at
+// most 240 MiB; 100 MiB with a viscosity contrast, where the rows wait for the
+// inside bits.  us per step on two queues and on one: FP32 128x128x64 55 and
+// 45, 144x144x64 58 and 59, 160x160x64 68 and 71; FP16 128x128x64 50 and 41,
+// 144x144x64 52 and 53, 192x192x80 54 and 71; FP64 96x96x64 65 and 55,
+// 112x112x64 73 and 69, 128x128x64 90 and 93; with a contrast 72x72x72 46 and
+// 42, 80x80x80 47 and 44, 96x96x96 49 and 50, 128x96x192 82 and 89.
 bool one_queue_size(const iblb_ctx *c) {
-    size_t pop_bytes = 0;
-    for (const BoxHost &H : c->plan.boxes) pop_bytes += 2 * (size_t)Q * H.plane * elem_bytes(c->plan.storage);
-    return c->plan.nblk > 0 && c->plan.nblk <= c->P.n_cus && pop_bytes <= (size_t)(c->P.contrast ? 32 : 100) << 20;
+    size_t cells = 0;
+    for (const BoxHost &H : c->plan.boxes) cells += H.plane;
+    const size_t pop_bytes = 2 * (size_t)Q * cells * elem_bytes(c->plan.storage);
+    return c->plan.nblk > 0 && c->plan.nblk <= c->P.n_cus && cells <= 1200000 &&
+           pop_bytes <= (size_t)(c->P.contrast ? 100 : 240) << 20;
 }
 bool uses_one_queue(const iblb_ctx *c) {
     const Launch D = default_launch(c), &L = c->L;
@@ -614,9 +620,10 @@ iblb_status enqueue_one_queue(iblb_ctx *c, hipStream_t s, int parity, bool advec
     for (int k = 0; k < n; ++k) {
         const int p = parity ^ (k & 1), adv = (advect_first || k > 0) ? 1 : 0;
         // shares of the row groups, in hundredths, beside the move, node and
-        // band work (128x128x64 in FP16: 42.2 us per step, with 35/30/35 44.6,
-        // with 50/5/45 43.2)
-        int share[3] = {45, 15, 40};
+        // band work (128x128x64 in FP32 44.9 us per step, with 45/15/40 46.6,
+        // with 35/15/50 46.0, with 50/10/40 47.6; in FP16 41.2, 40.8, 41.9 and
+        // 41.4)
+        int share[3] = {40, 20, 40};
         if (!adv || c->P.contrast) share[0] = 0;
         if (c->P.contrast && !c->P.penalty) share[1] = 0;  // the inside bits come with the forces
         const int64_t sum = share[0] + share[1] + share[2];

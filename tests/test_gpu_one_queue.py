@@ -32,6 +32,8 @@ CASES = {
                        [_drop(0, 3, 6.0, (20, 12, 10), theta=180.0)]),
     "contrast": lambda: ([Box(40, 32, 70, tau=1.0, tau_in=1.6)], [_drop(0, 3, 7.0, (39.3, 16.2, 30.4))]),
     "contrast_penalty": lambda: ([Box(36, 32, 24, tau=1.0, tau_in=0.7)], [_drop(0, 3, 7.0, (18.3, 16.2, 9.4), 1e-3)]),
+    "large": lambda: ([Box(125, 120, 68, tau=0.8)], [_drop(0, 5, 22.0, (60.2, 61.1, 22.7), 2e-3)]),
+    "large_contrast": lambda: ([Box(90, 80, 70, tau=1.0, tau_in=1.6)], [_drop(0, 4, 16.0, (85.3, 40.2, 30.4))]),
     "boxes": lambda: ([Box(32, 24, 20, tau=0.8), Box(20, 12, 16, tau=0.9), Box(70, 20, 24, tau=0.7, zbc=1)],
                       [_drop(0, 3, 6.0, (16, 12, 7)), _drop(2, 2, 5.0, (60, 10, 12), 1e-3, 180.0),
                        _drop(2, 1, 3.0, (20, 10, 12), theta=180.0)]),
