@@ -113,7 +113,31 @@ struct Plan {
     // the same per-step arrays inside the fixed scratch (iblb_step_static)
     size_t st_tri_part = 0, st_bbox = 0, st_breg = 0, st_part = 0, st_tile_list = 0,
            st_tile_count = 0, st_tcand = 0, st_tncand = 0, st_scan = 0, st_total = 0;
+    int reg_cells = MAXP;  // most cells of a node block's partial-spread region
 };
+
+// Layout of iblb_step_static's arrays in the fixed scratch with regions of
+// reg_cells cells, `first` Reals per triangle in front; returns its size.
+size_t static_layout(Plan &p, int reg_cells, int first) {
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        o = round_up(o, ALIGN);
+        const size_t r = o;
+        o += std::max<size_t>(bytes, 1);
+        return r;
+    };
+    if (first > 0) (void)take((size_t)first * p.Ttot * p.real);
+    p.st_tri_part = take(2 * (size_t)p.n_chunks * 8);
+    p.st_bbox = take(6 * (size_t)p.nblk * 4);
+    p.st_breg = take((size_t)BREG * p.nblk * 4);
+    p.st_part = take((size_t)3 * reg_cells * p.nblk * p.real);
+    p.st_tile_list = take((size_t)p.total_tiles * 8);
+    p.st_tile_count = take(2 * 4);
+    p.st_tcand = take((size_t)p.total_tiles * MAXC * 4);
+    p.st_tncand = take((size_t)2 * p.total_tiles * 4);
+    p.st_scan = take((size_t)2 * p.boxes.size() * 4);
+    return round_up(o, ALIGN);
+}
 
 bool finite(double v) { return std::isfinite(v); }
 
@@ -372,6 +396,14 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
             for (int k = 0; k < 2; ++k) H.off_mask[k] = take((size_t)H.nzw * H.b.ny * H.b.nx * 8);
         }
     }
+    // Few blocks: regions as large as their LDS holds (few_blocks), unless
+    // iblb_step_static's fixed scratch would only do with smaller ones.  What
+    // it counts against the scratch is what it always was (regions of MAXP
+    // cells and 20 Reals per triangle, once their records), so that a
+    // configuration is refused or taken as before.
+    p.reg_cells = p.nblk > FEW_BLOCKS ? MAXP : (p.real == 4 ? REG_MAX<float> : REG_MAX<double>);
+    p.st_total = static_layout(p, MAXP, 20);
+    if (p.st_total <= SCRATCH_BYTES && static_layout(p, p.reg_cells, 0) > SCRATCH_BYTES) p.reg_cells = MAXP;
     p.off_boxes = take(sizeof(BoxDev) * p.boxes.size());
     p.off_drops = take(sizeof(DropDev) * std::max<size_t>(p.drops.size(), 1));
     const size_t N = (size_t)p.Ntot;
@@ -384,7 +416,7 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_base = take(3 * N * 4);
     p.off_bbox = take(6 * (size_t)p.nblk * 4);
     p.off_breg = take((size_t)BREG * p.nblk * 4);
-    p.off_part = take((size_t)3 * MAXP * p.nblk * p.real);
+    p.off_part = take((size_t)3 * p.reg_cells * p.nblk * p.real);
     p.off_blk_drop = take((size_t)p.nblk * 8);
     p.off_node_of = take(N * 4);
     p.off_tri = take(3 * (size_t)p.Ttot * 4);
@@ -407,20 +439,7 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_obs_part2 = take((size_t)OBS_PASS2 * p.n_chunks * 8);
     p.off_uout = take(3 * N * 8);
     p.total = round_up(o, ALIGN);
-    o = 0;
-    // 20 Reals per triangle stay counted (they were per-triangle records),
-    // so that a configuration is refused or taken as it always was
-    (void)take((size_t)20 * p.Ttot * p.real);
-    p.st_tri_part = take(2 * (size_t)p.n_chunks * 8);
-    p.st_bbox = take(6 * (size_t)p.nblk * 4);
-    p.st_breg = take((size_t)BREG * p.nblk * 4);
-    p.st_part = take((size_t)3 * MAXP * p.nblk * p.real);
-    p.st_tile_list = take((size_t)p.total_tiles * 8);
-    p.st_tile_count = take(2 * 4);
-    p.st_tcand = take((size_t)p.total_tiles * MAXC * 4);
-    p.st_tncand = take((size_t)2 * p.total_tiles * 4);
-    p.st_scan = take((size_t)2 * p.boxes.size() * 4);
-    p.st_total = round_up(o, ALIGN);
+    (void)static_layout(p, p.reg_cells, 0);
     return IBLB_OK;
 }
 
@@ -1183,6 +1202,7 @@ static iblb_status init_device(iblb_ctx *c) {
         HIPCHK(c, hipGetDevice(&dev));
         HIPCHK(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         P.n_cus = std::max(cus, 1);
+        P.reg_cells = p.nblk <= P.n_cus ? p.reg_cells : MAXP;
         HIPCHK(c, scratch_address(dev, &c->scratch));
     }
 

@@ -257,7 +257,7 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
                     if (zper && dz < 0) dz += nz;
                     const int ex = br[3], ey = br[4], ez = br[5];
                     if (dx < ex && dy < ey && dz >= 0 && dz < ez) {
-                        const int64_t c = (int64_t)blk * 3 * MAXP + 3 * ((dz * ey + dy) * ex + dx);
+                        const int64_t c = (int64_t)blk * 3 * P.reg_cells + 3 * ((dz * ey + dy) * ex + dx);
                         v[k][0] = part[c];
                         v[k][1] = part[c + 1];
                         v[k][2] = part[c + 2];
@@ -339,7 +339,7 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
                 if (zper && dz < 0) dz += nz;
                 const int ex = bcast_i(ra.w, l), ey = bcast_i(rb.x, l), ez = bcast_i(rb.y, l);
                 if (dx < ex && dy < ey && dz >= 0 && dz < ez) {
-                    const int64_t c = (int64_t)bcast_i(blk_of, l) * 3 * MAXP + 3 * ((dz * ey + dy) * ex + dx);
+                    const int64_t c = (int64_t)bcast_i(blk_of, l) * 3 * P.reg_cells + 3 * ((dz * ey + dy) * ex + dx);
                     v[k][0] = part[c];
                     v[k][1] = part[c + 1];
                     v[k][2] = part[c + 2];

@@ -45,7 +45,13 @@ constexpr int NODE_BITS = 30;     // csr_nb: node id, and the corner above it
 constexpr int NODE_MASK = (1 << NODE_BITS) - 1;
 constexpr int TRI_CHUNK = 256;   // triangles per FP64 partial-sum chunk
 constexpr int K1_MAX_THREADS = 256; // launch bound of the bulk stream-collide kernel
-constexpr int MAXP = 2048;          // cells of a node block's partial-spread region
+constexpr int MAXP = 2048;          // most cells of a node block's partial-spread region
+constexpr int FEW_BLOCKS = 256;     // with at most this many blocks (and compute units): REG_MAX
+// The same with few blocks.  As a droplet spreads its blocks stretch, and a
+// block beyond the region is summed node by node in every tile it meets:
+// 128x128x64 with 161 blocks, FP16, 41.6 us per step as a sphere and 62 to 65
+// after 5,000 steps with regions of 2,048 cells, 50 with these.
+template <typename R> constexpr int REG_MAX = sizeof(R) == 4 ? 3200 : 2944;
 constexpr int BREG = 8;
 constexpr int MAXC = 16;           // node blocks recorded per band tile (more: the gather scans)
 constexpr int SCAN_GROUP = 256;    // boxes with at most this many node blocks: the gather scans them all
@@ -188,7 +194,7 @@ struct DevPtrs {
     int32_t *base;              // floor(q - 1/2), unwrapped (inspection)
     int32_t *bbox;              // [6][nblk]: x0,x1,y0,y1,z0,z1 of stencil cells
     int32_t *breg;              // [nblk][BREG]: partial region x0,y0,z0 (wrapped), ex,ey,ez, overflow
-    void *part;                 // [nblk][3][MAXP] partial spread regions (Real)
+    void *part;                 // [nblk][3][reg_cells] partial spread regions (Real)
     int32_t *blk_drop;          // [nblk][2]: droplet and box of each node block
     int32_t *node_of;           // [Ntot] per droplet: caller's node id -> global node id
     int32_t *tri;               // [Ttot][3] global node ids
@@ -214,6 +220,7 @@ struct DevPtrs {
     int32_t contrast;           // some box has tau_in set
     int32_t penalty;            // some droplet has a volume penalty
     int32_t moving;             // some box has a moving wall
+    int32_t reg_cells;          // most cells of a block's region
     int32_t mesh_lds;           // least LDS (bytes) of a workgroup of the mesh kernels beside the bulk kernel
     int32_t mask_words;         // largest nzw*ny*nx over those boxes
     int32_t pad_rows;           // some row group runs into its row's padding (x1 > nx)

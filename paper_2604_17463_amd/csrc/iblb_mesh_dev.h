@@ -281,7 +281,7 @@ __device__ __forceinline__ void move_role(const DevPtrs &P, int blk, bool first_
         clip_z(zper, nz, zl, zh);
         if (wave == 0 && lane == 0) {
             const int ex = bh[0] - bl[0] + 1, ey = bh[1] - bl[1] + 1, ez = zh - zl + 1;
-            const bool ovf = ex > nx || ey > ny || (zper && ez > nz) || ez < 1 || (int64_t)ex * ey * ez > MAXP;
+            const bool ovf = ex > nx || ey > ny || (zper && ez > nz) || ez < 1 || (int64_t)ex * ey * ez > P.reg_cells;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 P.bbox[(2 * a) * nb + blk] = bl[a];
@@ -464,7 +464,8 @@ __device__ __forceinline__ void compact_role(const DevPtrs &P, int item, int par
 // triangle over all nodes, instead of once in a pass that writes a record of
 // five four-vectors per triangle (160 B per node written, 290 B read back).
 // Cells of the LDS copies together.  FEW (at most one block per compute unit):
-// 80 KB, which holds all four sets of a box of up to 1,600 cells and leaves
+// 80 KB, which holds all four sets of a box of up to 1,600 cells (two at a
+// time of one up to REG_MAX) and leaves
 // room for two workgroups per CU; else a largest region once (29 KB in FP32).
 template <typename R, bool FEW> constexpr int REG_CELLS = FEW ? (sizeof(R) == 4 ? 6400 : 2944) : MAXP;
 template <typename R, bool FEW> struct NodeLds {
@@ -585,6 +586,7 @@ __device__ __forceinline__ void node_role(const DevPtrs &P, int blk, char *lds) 
     const bool ovf = SPREAD && br[6] != 0;
     const int ncell = ovf ? 0 : ex * ey * ez;
     constexpr int sets = !FEW ? 1 : (sizeof(R) == 4 ? 4 : 2), cells = REG_CELLS<R, FEW>;
+    static_assert(cells >= (FEW ? (sets >= 4 ? 2 : 1) * REG_MAX<R> : MAXP), "one copy fits; two with four sets");
     const int copies = sets >= 4 && 4 * ncell <= cells ? 4 : (sets >= 2 && 2 * ncell <= cells ? 2 : 1);
     if (wave == 0) {
         const int n_exp = D.n_exp, m_exp = D.m_exp;
@@ -700,11 +702,10 @@ __device__ __forceinline__ void node_role(const DevPtrs &P, int blk, char *lds) 
         __syncthreads();
         if (ovf) return;
         const int nv = min(NB, n_nodes - (blk * NB - node_off));
-        IBLB_GLOBAL R *out = (IBLB_GLOBAL R *)P.part + (int64_t)blk * 3 * MAXP;
+        IBLB_GLOBAL R *out = (IBLB_GLOBAL R *)P.part + (int64_t)blk * 3 * P.reg_cells;
         if constexpr (sets >= 4) {
             if (copies == 4) spread_block<R, FEW, 4>(S, ex, ey, ez, nv, sets, wave, lane, out);
             else spread_block<R, FEW, 2>(S, ex, ey, ez, nv, sets, wave, lane, out);
-            static_assert(sets < 4 || cells >= 2 * MAXP, "two copies always fit");
         } else {
             if (sets == 2 && copies == 2) spread_block<R, FEW, 2>(S, ex, ey, ez, nv, sets, wave, lane, out);
             else spread_block<R, FEW, 1>(S, ex, ey, ez, nv, sets, wave, lane, out);
