@@ -329,11 +329,11 @@ iblb_status iblb_load_state(struct iblb_ctx *ctx, const void *blob, size_t bytes
  *                     then recomputes the band tiles (not with tau_in).
  * Other values return IBLB_E_INVAL.  Rebuilds the step graphs.  Synchronising.
  * Results do not depend on the configuration.  With the launch that
- * iblb_init sets where nothing is tuned, a small context (both population
- * buffers at most 100 MiB, at most one node block of 64 nodes per compute
- * unit) runs a step as a line of launches on the caller's stream, the
- * stream-collide's rows beside the mesh work of each; any other launch runs
- * the schedule it names. */
+ * iblb_init sets where nothing is tuned, a small context (at most 1.2 million
+ * cells, both population buffers at most 240 MiB, 100 MiB with tau_in, at most
+ * one node block of 64 nodes per compute unit) runs a step as a line of
+ * launches on the caller's stream, the stream-collide's rows beside the mesh
+ * work of each; any other launch runs the schedule it names. */
 iblb_status iblb_set_launch(struct iblb_ctx *ctx, int32_t threads_x, int32_t rows_per_group,
                             int32_t cells_per_thread, int32_t streaming_stores,
                             int32_t max_workgroups, int32_t band_after_bulk);

@@ -214,8 +214,8 @@ __global__ void __launch_bounds__(K1_MAX_THREADS) __attribute__((amdgpu_waves_pe
 // GROUP: beside the bulk kernel one group at a time, because the band
 // kernel's waves share the compute units with the bulk kernel's and have to
 // fit where one of those has ended.  Four at a time took 103 VGPRs instead of
-// 82 and the steps became longer: shear 128x96x192 89 against 81 us,
-// 128x128x64 51 against 49 us; 250x250x150 (band kernel 65 -> 262 us).
+// 82 and the steps became longer: 256x256x128 BF16 179 against 160 us,
+// 250x250x150 312 against 293, 64 boxes of 128x128x64 973 against 967.
 // Against tests that loaded each bound behind the one before it, the band
 // kernel of 160 blocks alone went from 14.2 to 11.8 us.
 constexpr int SCAN_GROUPS = SCAN_GROUP / 64;
@@ -754,10 +754,10 @@ static int band_groups(const DevPtrs &P) { return std::min((P.total_tiles + 3) /
 // tiles start first and nothing follows them, so each wave gets about one
 // (128x128x64 with 160 node blocks: 4,096 workgroups 54 us per step, 640 50
 // us).  Beside the bulk kernel, which takes longer, a wave takes about four
-// one after another; per step with up to 8,192 workgroups and with one per
-// node block: 250x250x150 FP32 303.6 and 300.3 us, 256x256x128 BF16 183.7
-// and 180.5, 128x96x192 FP32 with a contrast 81.3 and 79.8, 64 boxes of
-// 128x128x64 1,037 and 1,022, 512x512x256 with 27 droplets 1,893 and 1,889.
+// one after another; us per step with eight workgroups per node block, with
+// four and with one: 256x256x128 BF16 176, 170 and 160, 64 boxes of 128x128x64
+// FP32 985, 984 and 964, 250x250x150 291, 290 and 290, 256x256x128 FP64 481,
+// 481 and 478, 512x512x256 with 16 droplets 1,866, 1,867 and 1,862.
 static int shared_band_groups(const DevPtrs &P, int per) {
     return std::max(1, std::min((P.total_tiles + 3) / 4, std::min(std::max(per * P.nblk, std::min(16 * P.nblk, 256)), BAND_GRID)));
 }
