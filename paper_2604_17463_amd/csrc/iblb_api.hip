@@ -457,11 +457,10 @@ struct iblb_ctx {
     Launch L{};
     bool one_queue = false;  // the steps run as a line of fused launches (uses_one_queue)
     hipGraphExec_t exec[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // [parity][advect first]
-    // MULTI_LEN[i] consecutive steps from a pending advection, by starting
-    // parity: one launch instead of MULTI_LEN[i] (the host cost of a launch
+    // MULTI_LEN[i] consecutive steps, [parity][advect first]: one launch instead of MULTI_LEN[i] (the host cost of a launch
     // is close to a step's device time at the sizes of the spreading
     // workload)
-    hipGraphExec_t multi[N_MULTI][2] = {};
+    hipGraphExec_t multi[N_MULTI][2][2] = {};
     bool pending = false;  // advection of the last step not yet applied
     int parity = 0;
     int64_t step = 0;
@@ -736,12 +735,13 @@ iblb_status flush(iblb_ctx *c) {
 }
 
 void drop_graphs(iblb_ctx *c) {
-    for (auto &row : c->multi)
-        for (auto &e : row)
-            if (e) {
-                (void)hipGraphExecDestroy(e);
-                e = nullptr;
-            }
+    for (auto &len : c->multi)
+        for (auto &row : len)
+            for (auto &e : row)
+                if (e) {
+                    (void)hipGraphExecDestroy(e);
+                    e = nullptr;
+                }
     for (auto &row : c->exec)
         for (auto &e : row)
             if (e) {
@@ -750,7 +750,14 @@ void drop_graphs(iblb_ctx *c) {
             }
 }
 
-iblb_status build_graphs(iblb_ctx *c) {
+// from_rest: also the multi-step graphs of runs that start without a pending
+// advection (the first after a call that reads or sets state), so that such a
+// run does not begin with a step of its own: the first step of each graph
+// waits for the graph before it and its chain runs beside no bulk kernel (with
+// the log of observables and positions, 20 steps of 256x256x128 in BF16 3,546
+// -> 3,475 us in two graphs instead of four, 40 steps of 250x250x150 in FP32
+// 12,212 -> 12,061 us in two instead of five).
+iblb_status build_graphs(iblb_ctx *c, bool from_rest = true) {
     drop_graphs(c);
     if (!(c->plan.flags & IBLB_FLAG_GRAPH)) return IBLB_OK;
     if (!c->capture) HIPCHK(c, hipStreamCreateWithFlags(&c->capture, hipStreamNonBlocking));
@@ -773,10 +780,11 @@ iblb_status build_graphs(iblb_ctx *c) {
         }
     if (c->plan.nblk == 0) return IBLB_OK;  // no advection: single steps only
     for (int li = 0; li < N_MULTI; ++li)
-        for (int p = 0; p < 2; ++p) {
+        for (int pa = from_rest ? 0 : 2; pa < 4; ++pa) {
+            const int p = pa & 1, a = pa >> 1;
             hipGraph_t g = nullptr;
             HIPCHK(c, hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal));
-            const iblb_status st = enqueue_steps(c, c->capture, p, true, MULTI_LEN[li]);
+            const iblb_status st = enqueue_steps(c, c->capture, p, a == 1, MULTI_LEN[li]);
             hipError_t e = hipStreamEndCapture(c->capture, &g);
             if (st != IBLB_OK) {
                 if (g) (void)hipGraphDestroy(g);
@@ -784,7 +792,7 @@ iblb_status build_graphs(iblb_ctx *c) {
             }
             if (e != hipSuccess)
                 return set_err(c, IBLB_E_DEVICE, std::string("graph capture: ") + hipGetErrorString(e));
-            e = hipGraphInstantiate(&c->multi[li][p], g, nullptr, nullptr, 0);
+            e = hipGraphInstantiate(&c->multi[li][p][a], g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             if (e != hipSuccess)
                 return set_err(c, IBLB_E_DEVICE, std::string("graph instantiate: ") + hipGetErrorString(e));
@@ -958,7 +966,7 @@ iblb_status autotune(iblb_ctx *c) {
             c->L = chosen = default_launch(c);
             iblb_status st = upload_rows(c);
             if (st == IBLB_OK) st = reset_state(c);
-            if (st == IBLB_OK) st = build_graphs(c);
+            if (st == IBLB_OK) st = build_graphs(c, false);
             if (st == IBLB_OK) st = time_steps(c, &sbest);
             if (st != IBLB_OK) return st;
         }
@@ -981,7 +989,7 @@ iblb_status autotune(iblb_ctx *c) {
                         if (L.maxg && c->L.grid >= c->P.n_rowgroups) continue;  // no cap at this size
                         double ms = 0;
                         st = reset_state(c);
-                        if (st == IBLB_OK) st = build_graphs(c);
+                        if (st == IBLB_OK) st = build_graphs(c, false);
                         if (st == IBLB_OK) st = time_steps(c, &ms);
                         if (st != IBLB_OK) return st;
                         if (ms < sbest) {
@@ -1461,11 +1469,11 @@ iblb_status iblb_step(iblb_ctx *c, int64_t n) {
         const int a = c->pending ? 1 : 0;
         const int p0 = c->parity;
         int64_t m = 0;
-        for (int li = 0; a && li < N_MULTI && !m; ++li)
-            if (n - k >= MULTI_LEN[li] && c->multi[li][p0]) {
-                // MULTI_LEN[li] steps, each starting with the previous
-                // step's advection
-                HIPCHK(c, hipGraphLaunch(c->multi[li][p0], c->stream));
+        for (int li = 0; li < N_MULTI && !m; ++li)
+            if (n - k >= MULTI_LEN[li] && c->multi[li][p0][a]) {
+                // MULTI_LEN[li] steps, each but the first of a run from rest
+                // starting with the previous step's advection
+                HIPCHK(c, hipGraphLaunch(c->multi[li][p0][a], c->stream));
                 m = MULTI_LEN[li];
             }
         if (!m && c->exec[p0][a]) {
