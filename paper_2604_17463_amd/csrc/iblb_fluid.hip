@@ -205,15 +205,17 @@ __global__ void __launch_bounds__(K1_MAX_THREADS) __attribute__((amdgpu_waves_pe
 //
 // The candidate blocks are the ones the move pass recorded for the tile
 // (sorted here); when the records are incomplete the stencil boxes of all
-// blocks of the box are tested, GROUP x 64 at a time.  Either way one
+// blocks of the box are tested, in passes of SCAN_GROUP.  Either way one
 // lane holds one block's region descriptor, loaded together and handed out
 // by lane reads, and the partial values of GATHER_BATCH blocks load side by
-// side.  Where a block of the batch has no region, the blocks are taken from
-// a list (the scan's in LDS) with their descriptors read one by one.
+// side.  Where a block of the pass has no region, the pass's blocks are taken
+// from a list (the scan's in LDS) with their descriptors read one by one, in
+// batches of GATHER_BATCH: a batch's blocks with a region, then those without.
+// The batches are those of the pass, so every launch adds in the same order.
 //
-// GROUP: beside the bulk kernel one group at a time, because the band
-// kernel's waves share the compute units with the bulk kernel's and have to
-// fit where one of those has ended.  Four at a time took 103 VGPRs instead of
+// GROUP: groups of 64 blocks tested together.  Beside the bulk kernel one,
+// because the band kernel's waves share the compute units with the bulk
+// kernel's and have to fit where one of those has ended.  Four at a time took 103 VGPRs instead of
 // 82 and the steps became longer: 256x256x128 BF16 179 against 160 us,
 // 250x250x150 312 against 293, 64 boxes of 128x128x64 973 against 967.
 // Against tests that loaded each bound behind the one before it, the band
@@ -356,6 +358,13 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
         }
     };
     const int4 *regs = (const int4 *)P.breg;  // two per block
+    // whether the stencil box of descriptor ra, rb meets the tile
+    auto meets_block = [&](int4 ra, int4 rb) {
+        const bool mx = meets_wrapped(ra.x, ra.w, x0, x1, nx, true);
+        const bool my = meets_wrapped(ra.y, rb.x, y0, y1, ny, true);
+        const bool mz = meets_wrapped(ra.z, rb.y, z0, z1, nz, zper);
+        return mx && my && mz;
+    };
 
     // the recorded candidates: count, flag and the MAXC slots (lane k holds
     // slot k) in one round trip
@@ -389,29 +398,31 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
         }
         return;
     }
-    for (int kb = b0; kb < b1; kb += 64 * GROUP) {
-        // every block's descriptor first, then the tests (a test that loads
-        // only where the one before it passed waits once per test)
-        int4 ra[GROUP], rb[GROUP];
+    for (int kp = b0; kp < b1; kp += SCAN_GROUP) {
+        const int ke = min(kp + SCAN_GROUP, b1);
+        const R G0 = F0, G1 = F1, G2 = F2;
+        bool any_ovf = false;
+        for (int kb = kp; kb < ke; kb += 64 * GROUP) {
+            // every block's descriptor first, then the tests (a test that
+            // loads only where the one before it passed waits once per test)
+            int4 ra[GROUP], rb[GROUP];
 #pragma unroll
-        for (int g = 0; g < GROUP; ++g) {
-            if (g > 0 && kb + 64 * g >= b1) continue;
-            const int mb = min(kb + 64 * g + lane, b1 - 1);
-            ra[g] = regs[2 * (int64_t)mb];
-            rb[g] = regs[2 * (int64_t)mb + 1];
-        }
-        uint64_t hit[GROUP], any_ovf = 0;
+            for (int g = 0; g < GROUP; ++g) {
+                if (g > 0 && kb + 64 * g >= ke) continue;
+                const int mb = min(kb + 64 * g + lane, ke - 1);
+                ra[g] = regs[2 * (int64_t)mb];
+                rb[g] = regs[2 * (int64_t)mb + 1];
+            }
+            uint64_t hit[GROUP], ovf = 0;
 #pragma unroll
-        for (int g = 0; g < GROUP; ++g) {
-            hit[g] = 0;
-            if (g > 0 && kb + 64 * g >= b1) continue;
-            const bool mx = meets_wrapped(ra[g].x, ra[g].w, x0, x1, nx, true);
-            const bool my = meets_wrapped(ra[g].y, rb[g].x, y0, y1, ny, true);
-            const bool mz = meets_wrapped(ra[g].z, rb[g].y, z0, z1, nz, zper);
-            hit[g] = __ballot(kb + 64 * g + lane < b1 && mx && my && mz);
-            any_ovf |= hit[g] & __ballot(rb[g].z != 0);
-        }
-        if (!any_ovf) {
+            for (int g = 0; g < GROUP; ++g) {
+                hit[g] = 0;
+                if (g > 0 && kb + 64 * g >= ke) continue;
+                hit[g] = __ballot(kb + 64 * g + lane < ke && meets_block(ra[g], rb[g]));
+                ovf |= hit[g] & __ballot(rb[g].z != 0);
+            }
+            any_ovf = ovf != 0;
+            if (any_ovf) break;
 #pragma unroll
             for (int g = 0; g < GROUP; ++g) {
                 uint64_t m = hit[g];
@@ -426,13 +437,19 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
                     add_lanes(ln, n, ra[g], rb[g], kb + 64 * g + lane);
                 }
             }
-            continue;
         }
+        if (!any_ovf) continue;
+        // a hit without a region: the whole pass again, its batches counted
+        // over all of its hits whatever GROUP is
+        F0 = G0;
+        F1 = G1;
+        F2 = G2;
         int total = 0;
-#pragma unroll
-        for (int g = 0; g < GROUP; ++g) {
-            if ((hit[g] >> lane) & 1) hits[total + __popcll(hit[g] & below)] = kb + 64 * g + lane;
-            total += __popcll(hit[g]);
+        for (int kb = kp; kb < ke; kb += 64) {
+            const int mb = min(kb + lane, ke - 1);
+            const uint64_t m = __ballot(kb + lane < ke && meets_block(regs[2 * (int64_t)mb], regs[2 * (int64_t)mb + 1]));
+            if ((m >> lane) & 1) hits[total + __popcll(m & below)] = kb + lane;
+            total += __popcll(m);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -441,7 +458,7 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
             auto id = [&](int k) { return __builtin_amdgcn_readfirstlane(hits[k0 + k]); };
             add_blocks(id, min(GATHER_BATCH, total - k0));
         }
-        __builtin_amdgcn_wave_barrier();  // the list is rewritten by the next group
+        __builtin_amdgcn_wave_barrier();  // the list is rewritten by the next pass
     }
 }
 
@@ -459,7 +476,7 @@ constexpr int BAND_GRID = 8192;
 // list in one contiguous eighth per XCD instead of interleaved.
 template <int ST, bool COLLIDE, bool ONE_BOX, int GROUP>
 __device__ __forceinline__ void band_role(const DevPtrs &P, int wg, int nwg, int parity, int full_u, float scale,
-                                          float inv, int xcd, int nt, int (*hits)[64 * GROUP]) {
+                                          float inv, int xcd, int nt, int (*hits)[SCAN_GROUP]) {
     using S = Stor<ST>;
     using R = typename S::R;
     constexpr uint32_t EB = sizeof(typename S::T);
@@ -587,7 +604,7 @@ __device__ __forceinline__ void band_role(const DevPtrs &P, int wg, int nwg, int
 template <int ST, bool COLLIDE, bool ONE_BOX>
 __global__ void __launch_bounds__(256)
     k_band(DevPtrs P, int parity, int full_u, float scale, float inv, int xcd, int nt) {
-    __shared__ int hits[4][64];
+    __shared__ int hits[4][SCAN_GROUP];
     band_role<ST, COLLIDE, ONE_BOX, 1>(P, blockIdx.x, gridDim.x, parity, full_u, scale, inv, xcd, nt, hits);
 }
 
@@ -621,7 +638,7 @@ struct FusedGrid {
 // LDS of a phase's mesh work, sized at launch (static LDS would claim VGPRs).
 template <typename R, int PHASE>
 constexpr int fused_lds = PHASE == PH_MOVE     ? MOVE_LDS
-                                          : PHASE == PH_BAND   ? (int)sizeof(int[4][64 * SCAN_GROUPS])
+                                          : PHASE == PH_BAND   ? (int)sizeof(int[4][SCAN_GROUP])
                                                : (int)sizeof(NodeLds<R, true>);
 extern __shared__ __align__(16) char lds[];
 
@@ -634,7 +651,7 @@ __global__ void __launch_bounds__(256, ST == 0 ? 1 : 4)
         if constexpr (PHASE == PH_MOVE)
             move_role<R, MOVE_STEP>(P, xcd_item(w, G.n0), w == 0, parity, 1, nullptr, lds);
         else if constexpr (PHASE == PH_BAND) {
-            auto hits = (int(*)[64 * SCAN_GROUPS])lds;
+            auto hits = (int(*)[SCAN_GROUP])lds;
             if (P.n_boxes == 1) band_role<ST, true, true, SCAN_GROUPS>(P, w, G.n0, parity, full_u, scale, inv, 0, nt, hits);
             else band_role<ST, true, false, SCAN_GROUPS>(P, w, G.n0, parity, full_u, scale, inv, 0, nt, hits);
         } else
