@@ -2181,13 +2181,15 @@ iblb_status iblb_time_mesh_chain(iblb_ctx *c, int32_t reps, double *ms) {
     c->last_step_epoch = -1;  // the band velocities no longer match the stamps
     HIPCHK(c, hipEventRecord(ev.a, c->stream));
     for (int r = 0; r < reps; ++r) {
-        // a fresh epoch each time, as the advection at the head of a step
-        // starts one; the nodes do not move (interpolation into a scratch U)
-        HIPCHK(c, launch_epoch(c->P, c->stream));
-        ++c->epoch;
+        // the nodes do not move (interpolation into a scratch U); a fresh
+        // epoch after each repetition, as the advection at the head of a step
+        // starts one: the next stamping pass must not meet these stamps and
+        // tile records
         const iblb_status st = enqueue_chain(c, c->P, c->parity, false, c->stream, nullptr);
         if (st != IBLB_OK) return st;
         HIPCHK(c, launch_move(c->P, f64, MOVE_U, c->parity, Udev, c->stream));
+        HIPCHK(c, launch_epoch(c->P, c->stream));
+        ++c->epoch;
     }
     HIPCHK(c, hipEventRecord(ev.b, c->stream));
     HIPCHK(c, hipEventSynchronize(ev.b));
