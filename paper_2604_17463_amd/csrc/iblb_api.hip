@@ -107,7 +107,8 @@ struct Plan {
            off_tile_list = 0, off_tile_count = 0, off_part = 0, off_breg = 0,
            off_base = 0, off_bbox = 0, off_blk_drop = 0, off_node_of = 0, off_tri = 0,
            off_csr_off = 0, off_csr_ent = 0, off_csr_nb = 0, off_chunks = 0, off_tri_part = 0, off_rows = 0,
-           off_tchunk = 0, off_tcand = 0, off_tncand = 0, off_scan = 0, off_ctr = 0, off_step_epoch = 0, off_status = 0, off_obs_groups = 0,
+           off_tchunk = 0, off_tcand = 0, off_tncand = 0, off_scan = 0, off_ctr = 0, off_step_epoch = 0, off_fast_tile = 0,
+           off_status = 0, off_obs_groups = 0,
            off_obs_part = 0, off_obs_part1 = 0, off_obs_part2 = 0,
            off_uout = 0, total = 0;
     // the same per-step arrays inside the fixed scratch (iblb_step_static)
@@ -432,6 +433,7 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_scan = take((size_t)2 * p.boxes.size() * 4);
     p.off_ctr = take(4);
     p.off_step_epoch = take(2 * 4);
+    p.off_fast_tile = take((size_t)p.total_tiles * 4);
     p.off_status = take(4);
     p.off_obs_groups = take(sizeof(ObsGroup) * (size_t)p.n_obs_groups);
     p.off_obs_part = take(2 * (size_t)p.n_obs_groups * 8);
@@ -564,6 +566,7 @@ int mesh_lds(const iblb_ctx *c) {
 // against 5.67 at 1024 cells per row).
 iblb_status upload_rows(iblb_ctx *c) {
     c->one_queue = uses_one_queue(c);
+    c->P.fast_tile = c->one_queue ? (int32_t *)(c->ws + c->plan.off_fast_tile) : nullptr;
     std::vector<RowGroup> rows;
     const int R = c->L.by * c->L.cpt, BX = c->L.bx;
     for (int b = 0; b < (int)c->plan.boxes.size(); ++b) {
@@ -1258,6 +1261,8 @@ static iblb_status init_device(iblb_ctx *c) {
         D.uw[3] = H.b.wall_hi[1];
         D.obs_begin = H.obs_begin;
         D.obs_end = H.obs_end;
+        D.fast_tile = (int32_t *)at(p.off_fast_tile) + H.tile_base;
+        D.ctr = (const int32_t *)at(p.off_ctr);
         const int64_t rows = (int64_t)H.b.ny * H.b.nz, ng = H.obs_end - H.obs_begin;
         for (int64_t k = 0; k < ng; ++k)
             og[H.obs_begin + k] = {(int32_t)b, (int32_t)(rows * k / ng), (int32_t)(rows * (k + 1) / ng), 0};
@@ -1371,6 +1376,7 @@ static iblb_status init_device(iblb_ctx *c) {
     HIPCHK(c, hipMemsetAsync(P.ctr, 0, 4, c->stream));
     // no epoch yet: 0xfefefefe matches neither an unstamped tile (-1) nor an epoch
     HIPCHK(c, hipMemsetAsync(P.step_epoch, 0xfe, 8, c->stream));
+    HIPCHK(c, hipMemsetAsync(at(p.off_fast_tile), 0xff, (size_t)p.total_tiles * 4, c->stream));
     HIPCHK(c, hipMemsetAsync(P.tile_count, 0, 8, c->stream));
     HIPCHK(c, hipMemsetAsync(P.tncand, 0, (size_t)2 * p.total_tiles * 4, c->stream));
     HIPCHK(c, hipMemsetAsync(P.scan_all, 0, (size_t)2 * p.boxes.size() * 4, c->stream));

@@ -27,7 +27,10 @@ namespace iblb {
 // none of their registers).  Without SKIP the kernel is the plain
 // stream-collide of every cell (boxes without droplets, timing).
 // NTM: 0 plain stores, 1 streaming, 2 as `nt` says.
-template <int ST, bool UROW, int NTM, int CPT, bool EXT, bool SKIP, bool PADW>
+// EARLY: the rows run before this step's stamps are known, and a speed that
+// only cells outside the band may not have is left to compact_role
+// (DevPtrs::fast_tile), under the epoch that the stamps will carry.
+template <int ST, bool UROW, int NTM, int CPT, bool EXT, bool SKIP, bool PADW, bool EARLY = false>
 __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST RowGroup &rg, int tx, int ty, int BX,
                                           int BY, int parity, int epoch, int full_u, float scale, float inv, int nt) {
     using S = Stor<ST>;
@@ -164,7 +167,16 @@ __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST Row
                     uf[2 * plane + e] = u[2];
                 }
                 if (!(rho > R(0) && rho < R(FLT_MAX))) atomicOr(P.status, BIT_RHO);
-                if (u[0] * u[0] + u[1] * u[1] + u[2] * u[2] > R(1) / R(3)) atomicOr(P.status, BIT_MACH);
+                if (u[0] * u[0] + u[1] * u[1] + u[2] * u[2] > R(1) / R(3)) {
+                    if constexpr (EARLY) {
+                        uint64_t bp = (uint64_t)B;
+                        asm volatile("" : "+s"(bp));  // keeps the loads in this branch
+                        const IBLB_CONST BoxDev *M = (const IBLB_CONST BoxDev *)bp;
+                        M->fast_tile[band_tile(xs, ryk[k], rzk[k], M->tnx, M->tny)] = *M->ctr + 1;
+                    } else {
+                        atomicOr(P.status, BIT_MACH);
+                    }
+                }
             }
             if constexpr (UROW) break;
         }
@@ -686,7 +698,7 @@ __global__ void __launch_bounds__(256, ST == 0 ? 1 : 4)
                                              : P.step_epoch[parity];
     const IBLB_CONST RowGroup *rows = (const IBLB_CONST RowGroup *)P.rows;
     const int BX = 1 << G.bxs;
-    bulk_rows<ST, true, 2, 1, EXT, SKIP, true>(P, rows[G.r0 + w], threadIdx.x & (BX - 1), threadIdx.x >> G.bxs, BX,
+    bulk_rows<ST, true, 2, 1, EXT, SKIP, true, !SKIP>(P, rows[G.r0 + w], threadIdx.x & (BX - 1), threadIdx.x >> G.bxs, BX,
                                                256 >> G.bxs, parity, epoch, full_u, scale, inv, nt);
 }
 

@@ -408,7 +408,9 @@ __device__ __forceinline__ void volume_role(const DevPtrs &P, int ci, double *sv
 // One wavefront per chunk of 64 tiles appends the chunk's stamped tiles to
 // the list of this epoch (one integer atomic per chunk; the order of the
 // list does not affect any result).  Item 0 also clears the other epoch's
-// count and names the epoch of this step's stamps.
+// count and names the epoch of this step's stamps.  A tile that rows computed
+// before the stamps marked as too fast without the spread force raises the
+// status here if it is not stamped; a stamped one is for the band to judge.
 __device__ __forceinline__ void compact_role(const DevPtrs &P, int item, int parity, int epoch) {
     const int lane = threadIdx.x & 63;
     const int c = __builtin_amdgcn_readfirstlane(item * 4 + (threadIdx.x >> 6));
@@ -419,12 +421,15 @@ __device__ __forceinline__ void compact_role(const DevPtrs &P, int item, int par
         for (int b = 0; b < P.n_boxes; ++b) P.scan_all[(slot ^ 1) * P.n_boxes + b] = 0;
     }
     if (c >= P.total_tiles / TILE_CELLS) return;
+    int fast = -1;  // loads beside the chunk's box
+    if (P.fast_tile) fast = P.fast_tile[c * TILE_CELLS + lane];
     // the next epoch's tile records start empty
     P.tncand[(int64_t)(slot ^ 1) * P.total_tiles + c * TILE_CELLS + lane] = 0;
     const int box = P.tchunk_box[c];
     const BoxDev &B = P.boxes[box];
     const int lt = c * TILE_CELLS + lane - B.tile_base;
     const bool st = lt < B.n_tiles && ((const IBLB_GLOBAL int32_t *)B.stamp[parity])[lt] == epoch;
+    if (fast == epoch && !st) atomicOr(P.status, BIT_MACH);
     const uint64_t m = __ballot(st);
     if (m == 0) return;
     int base = 0;
