@@ -212,7 +212,9 @@ __device__ __forceinline__ void drop_pass2(const DevPtrs &P, int ci, double (*sh
 // Mass and largest bare velocity of the current populations of one group of
 // rows.  Each wave takes whole rows (row addressing in scalar registers,
 // lanes along x).  The largest |j| / rho is found without a division per
-// cell: |j|^2 rho_best^2 against |j_best|^2 rho^2.
+// cell: |j|^2 rho_best^2 against |j_best|^2 rho^2; where those products could
+// leave the range of FP64, by the quotient itself.  A negative density or one
+// that is not a number gives no speed (the status word reports it).
 template <int ST>
 __device__ __forceinline__ void box_pass1(const DevPtrs &P, int gi, int parity, float inv, double (*sh)[2]) {
     using S = Stor<ST>;
@@ -229,6 +231,7 @@ __device__ __forceinline__ void box_pass1(const DevPtrs &P, int gi, int parity, 
     const uint64_t pb = (uint64_t)B->plane * sizeof(typename S::T);
     const int lane = threadIdx.x & 63, r1 = G.r1;
     double m = 0.0, bj = 0.0, br = 1.0;  // mass; |j|^2 and rho of the fastest cell
+    double far = 0.0;                    // largest quotient
     for (int r = __builtin_amdgcn_readfirstlane(G.r0 + (int)(threadIdx.x >> 6)); r < r1; r += 4) {
         const int z = r / ny, y = r - z * ny;
         const RowAddr ra = row_addr(y, z, ny, nz, sx, zper, sizeof(typename S::T));
@@ -246,14 +249,17 @@ __device__ __forceinline__ void box_pass1(const DevPtrs &P, int gi, int parity, 
             }
             m += dr;
             const double j2 = jx * jx + jy * jy + jz * jz, rho = rho0 + dr;
-            // a negative density gives no speed (the status word reports it)
-            if (rho >= 0.0 && j2 * (br * br) > bj * (rho * rho)) {
-                bj = j2;
-                br = rho;
+            if (j2 < 1e75 && rho < 1e75 && rho > 1e-75) {
+                if (j2 * (br * br) > bj * (rho * rho)) {
+                    bj = j2;
+                    br = rho;
+                }
+            } else {
+                far = fmax(far, sqrt(j2) / rho);
             }
         }
     }
-    double v[2] = {m, sqrt(bj) / br};
+    double v[2] = {m, fmax(sqrt(bj) / br, far)};
     block_reduce256(v, sh, [](int k, double a, double b) { return k == 0 ? a + b : fmax(a, b); });
     if (threadIdx.x == 0) {
         P.obs_part[2 * (int64_t)gi] = v[0];
