@@ -496,26 +496,6 @@ iblb_status set_err(iblb_ctx *c, iblb_status code, const std::string &msg) {
 
 bool is_f64(const iblb_ctx *c) { return c->plan.storage == IBLB_F64; }
 
-// Launch of a context whose launch nobody chose.
-Launch default_launch(const iblb_ctx *c) {
-    int nxmax = 0;
-    size_t pop_bytes = 0;
-    for (const BoxHost &H : c->plan.boxes) {
-        nxmax = std::max(nxmax, H.b.nx);
-        pop_bytes += 2 * (size_t)Q * H.plane * elem_bytes(c->plan.storage);
-    }
-    Launch L{};
-    // (32 threads along x only without droplets: the one-queue step's waves
-    // lie in one row each)
-    L.bx = nxmax <= 32 && c->plan.nblk == 0 ? 32 : (nxmax <= 64 ? 64 : (nxmax <= 128 ? 128 : 256));
-    L.by = 256 / L.bx;
-    // streaming stores once both population buffers exceed the 256 MiB
-    // last-level cache
-    L.nt = pop_bytes > ((size_t)256 << 20) ? 1 : 0;
-    L.cpt = 1;
-    return L;
-}
-
 // Whether the steps run as a line of fused launches on the caller's queue
 // (launch_fused, with the times on both sides of the line) instead of the
 // bulk kernel and the mesh chain on two: with the default launch, few node
@@ -532,6 +512,31 @@ bool one_queue_size(const iblb_ctx *c) {
     const size_t pop_bytes = 2 * (size_t)Q * cells * elem_bytes(c->plan.storage);
     return c->plan.nblk > 0 && c->plan.nblk <= c->P.n_cus && cells <= 1200000 &&
            pop_bytes <= (size_t)(c->P.contrast ? 100 : 240) << 20;
+}
+
+// Launch of a context whose launch nobody chose.
+Launch default_launch(const iblb_ctx *c) {
+    int nxmax = 0;
+    size_t pop_bytes = 0;
+    for (const BoxHost &H : c->plan.boxes) {
+        nxmax = std::max(nxmax, H.b.nx);
+        pop_bytes += 2 * (size_t)Q * H.plane * elem_bytes(c->plan.storage);
+    }
+    Launch L{};
+    // 32 threads along x for rows of at most 32 cells, but not in the one-queue
+    // step, whose waves lie in one row each, and with droplets not in two-byte
+    // storage, whose rows are padded to 64 cells.  us per step with 32 and 64:
+    // 300 boxes of 32x32x32 FP64 870 and 1,024, FP32 446 and 510, FP16 555 and
+    // 481; 60 of 30x30x30 158 and 161, 107 and 105, 107 and 107; 32x256x256
+    // with 64 droplets 267 and 288, 175 and 184, 185 and 191.
+    const bool narrow = nxmax <= 32 && !one_queue_size(c) && (c->plan.nblk == 0 || elem_bytes(c->plan.storage) > 2);
+    L.bx = narrow ? 32 : (nxmax <= 64 ? 64 : (nxmax <= 128 ? 128 : 256));
+    L.by = 256 / L.bx;
+    // streaming stores once both population buffers exceed the 256 MiB
+    // last-level cache
+    L.nt = pop_bytes > ((size_t)256 << 20) ? 1 : 0;
+    L.cpt = 1;
+    return L;
 }
 bool uses_one_queue(const iblb_ctx *c) {
     const Launch D = default_launch(c), &L = c->L;
