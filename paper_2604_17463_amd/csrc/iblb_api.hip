@@ -1026,10 +1026,11 @@ iblb_status autotune(iblb_ctx *c) {
 }
 
 // ---- autotune results kept across contexts ----
-// Key: the device (architecture, compute units), storage, graph use,
-// viscosity contrast and moving walls, and per box its dimensions, z
-// boundary and the node count of its droplets -- what the timed candidates
-// depend on.  Kept per process, and in the text file that the environment
+// Key: a version (raised when the candidates or what a launch selects
+// change), the device (architecture, compute units), storage, graph use,
+// viscosity contrast, moving walls and volume penalty, and per box its
+// dimensions, z boundary and the nodes and node blocks of its droplets --
+// what the timed candidates depend on.  Kept per process, and in the text file that the environment
 // variable IBLB_TUNE_CACHE names (one "key<TAB>launch" line per entry;
 // later lines win), so that repeated inits of one configuration time once.
 std::mutex g_tune_mu;
@@ -1041,14 +1042,17 @@ iblb_status tune_key(iblb_ctx *c, std::string *key) {
     hipDeviceProp_t prop;
     HIPCHK(c, hipGetDeviceProperties(&prop, dev));
     std::ostringstream k;
-    k << prop.gcnArchName << "/cu" << c->P.n_cus << "/st" << c->plan.storage << "/g"
-      << ((c->plan.flags & IBLB_FLAG_GRAPH) ? 1 : 0) << "/c" << c->P.contrast << "/m" << c->P.moving;
+    k << "v2/" << prop.gcnArchName << "/cu" << c->P.n_cus << "/st" << c->plan.storage << "/g"
+      << ((c->plan.flags & IBLB_FLAG_GRAPH) ? 1 : 0) << "/c" << c->P.contrast << "/m" << c->P.moving << "/p" << c->P.penalty;
     for (size_t b = 0; b < c->plan.boxes.size(); ++b) {
         const iblb_box &B = c->plan.boxes[b].b;
-        long nodes = 0;
+        long nodes = 0, blocks = 0;
         for (const DropHost &d : c->plan.drops)
-            if (d.d.box == (int)b) nodes += d.d.n_nodes;
-        k << "/" << B.nx << "x" << B.ny << "x" << B.nz << "z" << B.zbc << "n" << nodes;
+            if (d.d.box == (int)b) {
+                nodes += d.d.n_nodes;
+                blocks += d.n_blocks;
+            }
+        k << "/" << B.nx << "x" << B.ny << "x" << B.nz << "z" << B.zbc << "n" << nodes << "b" << blocks;
     }
     *key = k.str();
     return IBLB_OK;
