@@ -431,7 +431,7 @@ iblb_status build_plan(const iblb_config *cfg, Plan &p, std::string *err) {
     p.off_tcand = take((size_t)p.total_tiles * MAXC * 4);
     p.off_tncand = take((size_t)2 * p.total_tiles * 4);
     p.off_scan = take((size_t)2 * p.boxes.size() * 4);
-    p.off_ctr = take(4);
+    p.off_ctr = take(2 * 4);
     p.off_step_epoch = take(2 * 4);
     p.off_fast_tile = take((size_t)p.total_tiles * 4);
     p.off_status = take(4);
@@ -571,7 +571,6 @@ int mesh_lds(const iblb_ctx *c) {
 // against 5.67 at 1024 cells per row).
 iblb_status upload_rows(iblb_ctx *c) {
     c->one_queue = uses_one_queue(c);
-    c->P.fast_tile = c->one_queue ? (int32_t *)(c->ws + c->plan.off_fast_tile) : nullptr;
     std::vector<RowGroup> rows;
     const int R = c->L.by * c->L.cpt, BX = c->L.bx;
     for (int b = 0; b < (int)c->plan.boxes.size(); ++b) {
@@ -1205,6 +1204,7 @@ static iblb_status init_device(iblb_ctx *c) {
     P.scan_all = (int32_t *)at(p.off_scan);
     P.ctr = (int32_t *)at(p.off_ctr);
     P.step_epoch = (int32_t *)at(p.off_step_epoch);
+    P.fast_tile = (int32_t *)at(p.off_fast_tile);
     P.status = (uint32_t *)at(p.off_status);
     P.obs_groups = (ObsGroup *)at(p.off_obs_groups);
     P.obs_part = (double *)at(p.off_obs_part);
@@ -1270,8 +1270,8 @@ static iblb_status init_device(iblb_ctx *c) {
         D.uw[3] = H.b.wall_hi[1];
         D.obs_begin = H.obs_begin;
         D.obs_end = H.obs_end;
-        D.fast_tile = (int32_t *)at(p.off_fast_tile) + H.tile_base;
-        D.ctr = (const int32_t *)at(p.off_ctr);
+        D.fast_tile = P.fast_tile + H.tile_base;
+        D.ctr = P.ctr;
         const int64_t rows = (int64_t)H.b.ny * H.b.nz, ng = H.obs_end - H.obs_begin;
         for (int64_t k = 0; k < ng; ++k)
             og[H.obs_begin + k] = {(int32_t)b, (int32_t)(rows * k / ng), (int32_t)(rows * (k + 1) / ng), 0};
@@ -1383,9 +1383,10 @@ static iblb_status init_device(iblb_ctx *c) {
             HIPCHK(c, hipMemsetAsync(at(H.off_ufull), 0, (size_t)3 * H.plane * R, c->stream));
     }
     HIPCHK(c, hipMemsetAsync(P.ctr, 0, 4, c->stream));
+    HIPCHK(c, hipMemsetAsync(P.ctr + 1, 0xff, 4, c->stream));
     // no epoch yet: 0xfefefefe matches neither an unstamped tile (-1) nor an epoch
     HIPCHK(c, hipMemsetAsync(P.step_epoch, 0xfe, 8, c->stream));
-    HIPCHK(c, hipMemsetAsync(at(p.off_fast_tile), 0xff, (size_t)p.total_tiles * 4, c->stream));
+    HIPCHK(c, hipMemsetAsync(P.fast_tile, 0xff, (size_t)p.total_tiles * 4, c->stream));
     HIPCHK(c, hipMemsetAsync(P.tile_count, 0, 8, c->stream));
     HIPCHK(c, hipMemsetAsync(P.tncand, 0, (size_t)2 * p.total_tiles * 4, c->stream));
     HIPCHK(c, hipMemsetAsync(P.scan_all, 0, (size_t)2 * p.boxes.size() * 4, c->stream));

@@ -28,7 +28,7 @@ namespace iblb {
 // stream-collide of every cell (boxes without droplets, timing).
 // NTM: 0 plain stores, 1 streaming, 2 as `nt` says.
 // EARLY: the rows run before this step's stamps are known, and a speed that
-// only cells outside the band may not have is left to compact_role
+// only cells outside the band may not have is left to fast_role
 // (DevPtrs::fast_tile), under the epoch that the stamps will carry.
 template <int ST, bool UROW, int NTM, int CPT, bool EXT, bool SKIP, bool PADW, bool EARLY = false>
 __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST RowGroup &rg, int tx, int ty, int BX,
@@ -172,7 +172,9 @@ __device__ __forceinline__ void bulk_rows(const DevPtrs &P, const IBLB_CONST Row
                         uint64_t bp = (uint64_t)B;
                         asm volatile("" : "+s"(bp));  // keeps the loads in this branch
                         const IBLB_CONST BoxDev *M = (const IBLB_CONST BoxDev *)bp;
-                        M->fast_tile[band_tile(xs, ryk[k], rzk[k], M->tnx, M->tny)] = *M->ctr + 1;
+                        const int next = *M->ctr + 1;
+                        M->fast_tile[band_tile(xs, ryk[k], rzk[k], M->tnx, M->tny)] = next;
+                        M->ctr[1] = next;
                     } else {
                         atomicOr(P.status, BIT_MACH);
                     }
@@ -449,13 +451,16 @@ __device__ __forceinline__ void gather_F(const DevPtrs &P, const IBLB_CONST BoxD
                     add_lanes(ln, n, ra[g], rb[g], kb + 64 * g + lane);
                 }
             }
+            if constexpr (GROUP == SCAN_GROUPS) break;  // the whole pass
         }
         if (!any_ovf) continue;
         // a hit without a region: the whole pass again, its batches counted
         // over all of its hits whatever GROUP is
-        F0 = G0;
-        F1 = G1;
-        F2 = G2;
+        if constexpr (GROUP < SCAN_GROUPS) {
+            F0 = G0;
+            F1 = G1;
+            F2 = G2;
+        }
         int total = 0;
         for (int kb = kp; kb < ke; kb += 64) {
             const int mb = min(kb + lane, ke - 1);
@@ -643,7 +648,8 @@ __global__ void __launch_bounds__(256)
 // fill the chip with rows in every launch, and each launch ends with its own
 // tail.
 struct FusedGrid {
-    int n0, n1, n2;  // workgroups of the phase's three kinds of mesh work
+    int n0, n1, n2;  // workgroups of the phase's three kinds of mesh work; PH_BAND: n1 rows, then the fast tiles
+                     // (last: one workgroup before the rows made the launch 1 us longer at 128x128x64 FP32)
     int r0, bxs;     // first row group; log2 of the threads along x (64 to 256)
 };
 
@@ -691,6 +697,12 @@ __global__ void __launch_bounds__(256, ST == 0 ? 1 : 4)
             return;
         }
         w -= G.n2;
+    }
+    if constexpr (PHASE == PH_BAND) {
+        if (w == G.n1) {
+            fast_role(P, parity);
+            return;
+        }
     }
     constexpr bool SKIP = PHASE != PH_MOVE;
     const int epoch = PHASE == PH_MOVE       ? -2
@@ -843,7 +855,12 @@ static hipError_t launch_fused_p(const DevPtrs &P, int parity, int adv, int full
     } else {
         G.n0 = PHASE == PH_NODE ? P.nblk : shared_band_groups(P, 4);
     }
-    const dim3 grid(G.n0 + G.n1 + G.n2 + nrows), block(256);
+    int groups = G.n0 + G.n1 + G.n2 + nrows;
+    if (PHASE == PH_BAND) {
+        G.n1 = nrows;
+        ++groups;
+    }
+    const dim3 grid(groups), block(256);
     const float inv = 1.0f / scale;
     const size_t bytes = fused_lds<typename Stor<ST>::R, PHASE>;
     if (P.contrast || P.moving)

@@ -157,7 +157,7 @@ struct BoxDev {
     int32_t obs_begin, obs_end; // the box's row groups of the observables
     int32_t pad;
     int32_t *fast_tile;         // [n_tiles] the box's part of DevPtrs::fast_tile
-    const int32_t *ctr;         // DevPtrs::ctr
+    int32_t *ctr;               // DevPtrs::ctr
 };
 
 struct DropDev {
@@ -210,10 +210,10 @@ struct DevPtrs {
     int32_t *tcand;             // [total_tiles][MAXC] node blocks whose stencil box covers the tile
     int32_t *tncand;            // [2][total_tiles] their number, by epoch parity
     int32_t *scan_all;          // [2][n_boxes] some block of the box could not record its tiles
-    int32_t *ctr;               // epoch of the last band pass
+    int32_t *ctr;               // epoch of the last band pass; last epoch of any fast_tile
     int32_t *step_epoch;        // [2] epoch of the last stamps, by buffer parity
     int32_t *fast_tile;         // [total_tiles] last epoch in which a row computed before the stamps met a
-                                // bare speed above the sound speed in the tile (one-queue steps; else null)
+                                // bare speed above the sound speed in the tile
     uint32_t *status;
     ObsGroup *obs_groups;       // row groups of the observables, box by box
     double *obs_part;           // [n_obs_groups][2] mass, max_u

@@ -408,9 +408,7 @@ __device__ __forceinline__ void volume_role(const DevPtrs &P, int ci, double *sv
 // One wavefront per chunk of 64 tiles appends the chunk's stamped tiles to
 // the list of this epoch (one integer atomic per chunk; the order of the
 // list does not affect any result).  Item 0 also clears the other epoch's
-// count and names the epoch of this step's stamps.  A tile that rows computed
-// before the stamps marked as too fast without the spread force raises the
-// status here if it is not stamped; a stamped one is for the band to judge.
+// count and names the epoch of this step's stamps.
 __device__ __forceinline__ void compact_role(const DevPtrs &P, int item, int parity, int epoch) {
     const int lane = threadIdx.x & 63;
     const int c = __builtin_amdgcn_readfirstlane(item * 4 + (threadIdx.x >> 6));
@@ -421,15 +419,12 @@ __device__ __forceinline__ void compact_role(const DevPtrs &P, int item, int par
         for (int b = 0; b < P.n_boxes; ++b) P.scan_all[(slot ^ 1) * P.n_boxes + b] = 0;
     }
     if (c >= P.total_tiles / TILE_CELLS) return;
-    int fast = -1;  // loads beside the chunk's box
-    if (P.fast_tile) fast = P.fast_tile[c * TILE_CELLS + lane];
     // the next epoch's tile records start empty
     P.tncand[(int64_t)(slot ^ 1) * P.total_tiles + c * TILE_CELLS + lane] = 0;
     const int box = P.tchunk_box[c];
     const BoxDev &B = P.boxes[box];
     const int lt = c * TILE_CELLS + lane - B.tile_base;
     const bool st = lt < B.n_tiles && ((const IBLB_GLOBAL int32_t *)B.stamp[parity])[lt] == epoch;
-    if (fast == epoch && !st) atomicOr(P.status, BIT_MACH);
     const uint64_t m = __ballot(st);
     if (m == 0) return;
     int base = 0;
@@ -439,6 +434,23 @@ __device__ __forceinline__ void compact_role(const DevPtrs &P, int item, int par
     if (st && k < P.total_tiles) {  // one entry per tile and epoch: k < total_tiles always
         P.tile_list[2 * k] = c * TILE_CELLS + lane;
         P.tile_list[2 * k + 1] = box;
+    }
+}
+
+// ------------------------------------------------------------- fast tiles
+// One workgroup beside the band tiles of the one-queue step: if rows computed
+// before the stamps met a bare speed above the sound speed, the tiles they
+// marked raise the status unless they are stamped; a stamped one is for the
+// band to judge.  (In a workgroup of its own because it is on no path there:
+// beside the tile list the check cost 128x128x64 in FP32 0.4 us per step.)
+__device__ __forceinline__ void fast_role(const DevPtrs &P, int parity) {
+    const int epoch = ((const IBLB_CONST int32_t *)P.step_epoch)[parity];
+    if (P.ctr[1] != epoch) return;
+    for (int b = 0; b < P.n_boxes; ++b) {
+        const BoxDev &B = P.boxes[b];
+        const IBLB_GLOBAL int32_t *stamp = (const IBLB_GLOBAL int32_t *)B.stamp[parity];
+        for (int t = threadIdx.x; t < B.n_tiles; t += 256)
+            if (B.fast_tile[t] == epoch && stamp[t] != epoch) atomicOr(P.status, BIT_MACH);
     }
 }
 
