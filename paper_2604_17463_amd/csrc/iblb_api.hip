@@ -757,13 +757,17 @@ void drop_graphs(iblb_ctx *c) {
             }
 }
 
-// from_rest: also the multi-step graphs of runs that start without a pending
+// from_rest: also multi-step graphs of runs that start without a pending
 // advection (the first after a call that reads or sets state), so that such a
 // run does not begin with a step of its own: the first step of each graph
-// waits for the graph before it and its chain runs beside no bulk kernel (with
-// the log of observables and positions, 20 steps of 256x256x128 in BF16 3,546
-// -> 3,475 us in two graphs instead of four, 40 steps of 250x250x150 in FP32
-// 12,212 -> 12,061 us in two instead of five).
+// waits for the graph before it and, on two queues, its chain runs beside no
+// bulk kernel.  On two queues only of 8 and 16 steps, because their graphs make
+// init longer.  Without them, with 8 alone, with both and with one of each
+// length: 20 steps of 256x256x128 in BF16 3,337, 3,305, 3,252 and 3,270 us, 10
+// of 250x250x150 in FP32 3,037, 2,978, 2,976 and 2,979, 50 of 128x96x192 with a
+// contrast 4,059, 4,047, 4,021 and 4,027; init of the last 15.0, 15.7, 16.3 and
+// 17.4 ms.  In the one-queue step, whose graphs build faster, all of them: 100
+// steps of 128x128x64 in FP16 4,186 us without, 4,157 with.
 iblb_status build_graphs(iblb_ctx *c, bool from_rest = true) {
     drop_graphs(c);
     if (!(c->plan.flags & IBLB_FLAG_GRAPH)) return IBLB_OK;
@@ -789,6 +793,7 @@ iblb_status build_graphs(iblb_ctx *c, bool from_rest = true) {
     for (int li = 0; li < N_MULTI; ++li)
         for (int pa = from_rest ? 0 : 2; pa < 4; ++pa) {
             const int p = pa & 1, a = pa >> 1;
+            if (a == 0 && !c->one_queue && MULTI_LEN[li] != 8 && MULTI_LEN[li] != 16) continue;
             hipGraph_t g = nullptr;
             HIPCHK(c, hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal));
             const iblb_status st = enqueue_steps(c, c->capture, p, a == 1, MULTI_LEN[li]);
