@@ -218,12 +218,14 @@ iblb_status iblb_step(struct iblb_ctx *ctx, int64_t n_steps);
  * the library, 32 MiB per GPU, held from the library's load until the
  * process ends, instead of from the context's workspace.  Allocates
  * nothing and replays no graph: the kernels of each step are enqueued on
- * the context's stream one after another, with the step's advection
- * applied at its end.  The step scratch counted for a configuration grows
- * with its nodes (about 560 B per node in FP32, 1.1 KB in FP64) and its box cells
- * (1.25 B per cell): the 128x128x64 spreading workload needs about 7 MB.
- * One that exceeds 32 MiB returns IBLB_E_WORKSPACE with the bytes it
- * needs.  The array is shared by every
+ * the context's stream one after another, each step's advection at the head
+ * of the next one, the last step's at the end of the call.  The step scratch
+ * counted for a configuration grows with its nodes (about 560 B per node in
+ * FP32, 1.1 KB in FP64) and its box cells (1.25 B per cell): the 128x128x64
+ * spreading workload counts as about 7 MB.  The count includes 20 values per
+ * triangle that earlier versions kept there, so that the same configurations
+ * are taken in every version; one that exceeds 32 MiB returns
+ * IBLB_E_WORKSPACE with its count.  The array is shared by every
  * context on the GPU and keeps the last call's contents (the records that
  * must start empty are cleared by each call): calls that overlap on one
  * GPU, from any context or thread, race.  Asynchronous like iblb_step. */
@@ -324,13 +326,16 @@ iblb_status iblb_load_state(struct iblb_ctx *ctx, const void *blob, size_t bytes
  *   band_after_bulk   0: the cells of the band tiles (those within reach of a
  *                     node's stencil) are computed by the band kernel beside
  *                     the stream-collide of the other cells, which waits for
- *                     the step's node pass; 1: the stream-collide runs over
+ *                     the step's tile stamps; 1: the stream-collide runs over
  *                     every cell beside the mesh kernels and the band kernel
- *                     then recomputes the band tiles (not with tau_in).
+ *                     then recomputes the band tiles (not with tau_in).  With
+ *                     1 a band cell also sets IBLB_BIT_MACH when it exceeds
+ *                     the sound speed only without its spread force.
  * Other values return IBLB_E_INVAL.  Rebuilds the step graphs.  Synchronising.
  * Results do not depend on the configuration.  With the launch that
  * iblb_init sets where nothing is tuned, a small context (at most 1.2 million
- * cells, both population buffers at most 240 MiB, 100 MiB with tau_in, at most
+ * elements in a population plane, that is cells with each row padded to 128
+ * bytes, both population buffers at most 240 MiB, 100 MiB with tau_in, at most
  * one node block of 64 nodes per compute unit) runs a step as a line of
  * launches on the caller's stream, the stream-collide's rows beside the mesh
  * work of each; any other launch runs the schedule it names. */

@@ -499,13 +499,16 @@ bool is_f64(const iblb_ctx *c) { return c->plan.storage == IBLB_F64; }
 // Whether the steps run as a line of fused launches on the caller's queue
 // (launch_fused, with the times on both sides of the line) instead of the
 // bulk kernel and the mesh chain on two: with the default launch, few node
-// blocks, at most 1.2 million cells and both population buffers together at
-// most 240 MiB; 100 MiB with a viscosity contrast, where the rows wait for the
-// inside bits.  us per step on two queues and on one: FP32 128x128x64 55 and
-// 45, 144x144x64 58 and 59, 160x160x64 68 and 71; FP16 128x128x64 50 and 41,
-// 144x144x64 52 and 53, 192x192x80 54 and 71; FP64 96x96x64 65 and 55,
-// 112x112x64 73 and 69, 128x128x64 90 and 93; with a contrast 72x72x72 46 and
-// 42, 80x80x80 47 and 44, 96x96x96 49 and 50, 128x96x192 82 and 89.
+// blocks, at most 1.2 million elements in a population plane (cells, each row
+// padded to 128 bytes) and both population buffers together at most 240 MiB;
+// 100 MiB with a viscosity contrast, where the rows wait for the inside bits.
+// us per step on two queues (the best of four launches) and on one: FP32
+// 32x32x24 31 and 23, 64x48x40 34 and 29, 96x96x64 46 and 36, 128x128x64 58 and
+// 45, 144x144x64 57 and 60, 160x160x64 67 and 71; FP16 128x128x64 50 and 42,
+// 144x144x64 52 and 56, 192x192x80 59 and 74; FP64 32x32x24 37 and 28, 96x96x64
+// 60 and 49, 112x112x64 71 and 65, 128x128x64 93 and 91; with a contrast
+// 72x72x72 43 and 34, 80x80x80 45 and 37, 96x96x96 (134 MiB) 51 and 45,
+// 128x96x192 82 and 87.
 bool one_queue_size(const iblb_ctx *c) {
     size_t cells = 0;
     for (const BoxHost &H : c->plan.boxes) cells += H.plane;
@@ -645,9 +648,11 @@ iblb_status enqueue_one_queue(iblb_ctx *c, hipStream_t s, int parity, bool advec
     for (int k = 0; k < n; ++k) {
         const int p = parity ^ (k & 1), adv = (advect_first || k > 0) ? 1 : 0;
         // shares of the row groups, in hundredths, beside the move, node and
-        // band work (128x128x64 in FP32 44.9 us per step, with 45/15/40 46.6,
-        // with 35/15/50 46.0, with 50/10/40 47.6; in FP16 41.2, 40.8, 41.9 and
-        // 41.4)
+        // band work.  us per step with these, 45/15/40, 35/15/50, 50/10/40 and
+        // 40/30/30: 128x128x64 FP32 45.7, 47.6, 45.7, 48.8, 47.2, FP16 42.2,
+        // 41.8, 42.9, 42.5, 43.3; 96x96x64 FP32 36.0, 36.1, 36.1, 36.4, 37.4,
+        // FP16 35.5, 35.6, 36.3, 35.9, 37.4, FP64 49.6, 50.9, 50.4, 51.7, 47.9;
+        // 64x48x40 and 32x32x24 within 0.3
         int share[3] = {40, 20, 40};
         if (!adv || c->P.contrast) share[0] = 0;
         if (c->P.contrast && !c->P.penalty) share[1] = 0;  // the inside bits come with the forces
@@ -1528,7 +1533,7 @@ iblb_status iblb_step_static(iblb_ctx *c, int64_t n) {
     const Plan &p = c->plan;
     if (p.st_total > SCRATCH_BYTES)
         return set_err(c, IBLB_E_WORKSPACE,
-                       "iblb_step_static: the configuration needs " + std::to_string(p.st_total) +
+                       "iblb_step_static: the configuration counts as " + std::to_string(p.st_total) +
                            " bytes of step scratch, the fixed scratch holds " + std::to_string(SCRATCH_BYTES));
     if (n == 0) return IBLB_OK;
     {
@@ -1566,8 +1571,9 @@ iblb_status iblb_step_static(iblb_ctx *c, int64_t n) {
     HIPCHK(c, launch_fill_i32(V.tncand, 0, 2 * (int64_t)p.total_tiles, s));
     HIPCHK(c, launch_fill_i32(V.tile_count, 0, 2, s));
     HIPCHK(c, launch_fill_i32(V.scan_all, 0, 2 * (int64_t)p.boxes.size(), s));
-    // one queue, in order: mesh chain, band tiles, every other cell, then the
-    // advection (none is left pending)
+    // one queue, in order: mesh chain (with the last step's advection at its
+    // head), band tiles, every other cell; after the last step its advection
+    // (none is left pending)
     for (int64_t k = 0; k < n; ++k) {
         const int par = c->parity;
         const iblb_status st = enqueue_chain(c, V, par, k > 0, s, nullptr);

@@ -114,16 +114,6 @@ template <typename R> struct Node3 {
     R h[3], l[3];
 };
 template <typename R>
-__device__ __forceinline__ Node3<R> load_node(const R *qh, const R *ql, int Ntot, int j) {
-    Node3<R> n;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        n.h[a] = qh[a * Ntot + j];
-        n.l[a] = ql[a * Ntot + j];
-    }
-    return n;
-}
-template <typename R>
 __device__ __forceinline__ void diff(const Node3<R> &b, const Node3<R> &a, R (&d)[3]) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) d[k] = (b.h[k] - a.h[k]) + (b.l[k] - a.l[k]);

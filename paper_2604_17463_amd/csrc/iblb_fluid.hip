@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(K1_MAX_THREADS) __attribute__((amdgpu_waves_pe
 // GROUP: groups of 64 blocks tested together.  Beside the bulk kernel one,
 // because the band kernel's waves share the compute units with the bulk
 // kernel's and have to fit where one of those has ended.  Four at a time took 103 VGPRs instead of
-// 82 and the steps became longer: 256x256x128 BF16 179 against 160 us,
+// 82 (84 now) and the steps became longer: 256x256x128 BF16 179 against 160 us,
 // 250x250x150 312 against 293, 64 boxes of 128x128x64 973 against 967.
 // Against tests that loaded each bound behind the one before it, the band
 // kernel of 160 blocks alone went from 14.2 to 11.8 us.
@@ -641,12 +641,10 @@ __global__ void __launch_bounds__(256)
 // overwritten by PH_BAND.  With a viscosity contrast rows can only follow the
 // inside bits.
 //
-// Measured per step against the two queues: 32x32x24 with 642 nodes FP32 31.2
-// -> 23.4 us, FP64 43.6 -> 35.0; 45x37x41 39.2 -> 31.0; 64x48x40 with 2,562
-// nodes 32.9 -> 28.4; 96x96x64 with 10,242 nodes 44.6 -> 41.2; 128x128x64 in
-// FP16 44.2 -> 42.2, in FP32 49.6 -> 50.4; 160x160x64 64 -> 76: larger boxes
-// fill the chip with rows in every launch, and each launch ends with its own
-// tail.
+// At 128x128x64 in FP32 a step takes 45 us so and 58 us on two queues; from
+// about 144x144x64 on two queues are faster: larger boxes fill the chip with
+// rows in every launch, and each launch ends with its own tail.  The rule that
+// chooses (one_queue_size) has the times on both sides.
 struct FusedGrid {
     int n0, n1, n2;  // workgroups of the phase's three kinds of mesh work; PH_BAND: n1 rows, then the fast tiles
                      // (last: one workgroup before the rows made the launch 1 us longer at 128x128x64 FP32)
@@ -791,10 +789,10 @@ static int band_groups(const DevPtrs &P) { return std::min((P.total_tiles + 3) /
 // 4), where empty workgroups take dispatch and room from the bulk rows: `per`
 // for each node block, as a block of 64 nodes about one cell apart covers 13
 // to 16 tiles, and more where few coarse blocks cover more (45x37x41 with 11
-// blocks: 44 workgroups 34 us per step, 176 31 us).  In one queue the band's
+// blocks: 44 workgroups 36 us per step, 176 33 us).  In one queue the band's
 // tiles start first and nothing follows them, so each wave gets about one
-// (128x128x64 with 160 node blocks: 4,096 workgroups 54 us per step, 640 50
-// us).  Beside the bulk kernel, which takes longer, a wave takes about four
+// (128x128x64 with 160 node blocks: 176 workgroups 56 us per step, 640 46, 4,096
+// 50).  Beside the bulk kernel, which takes longer, a wave takes about four
 // one after another; us per step with eight workgroups per node block, with
 // four and with one: 256x256x128 BF16 176, 170 and 160, 64 boxes of 128x128x64
 // FP32 985, 984 and 964, 250x250x150 291, 290 and 290, 256x256x128 FP64 481,

@@ -505,8 +505,8 @@ __device__ __forceinline__ double take(bool on, double a, double b) {
                                           (((uint64_t)__double_as_longlong(b)) & ~m)));
 }
 
-// x / 6, correctly rounded: a product with the rounded reciprocal and one
-// exact-remainder correction.
+// x / 6, correctly rounded (in FP32 for every x with a quotient above 1e-36): a
+// product with the rounded reciprocal and one exact-remainder correction.
 __device__ __forceinline__ float sixth(float x) {
     const float r = 1.0f / 6.0f, q = x * r;
     return __builtin_fmaf(__builtin_fmaf(-6.0f, q, x), r, q);
