@@ -1392,11 +1392,10 @@ static iblb_status init_device(iblb_ctx *c) {
         if (p.flags & IBLB_FLAG_FULL_U)
             HIPCHK(c, hipMemsetAsync(at(H.off_ufull), 0, (size_t)3 * H.plane * R, c->stream));
     }
-    HIPCHK(c, hipMemsetAsync(P.ctr, 0, 4, c->stream));
-    HIPCHK(c, hipMemsetAsync(P.ctr + 1, 0xff, 4, c->stream));
+    HIPCHK(c, hipMemsetAsync(P.ctr, 0, 8, c->stream));
     // no epoch yet: 0xfefefefe matches neither an unstamped tile (-1) nor an epoch
     HIPCHK(c, hipMemsetAsync(P.step_epoch, 0xfe, 8, c->stream));
-    HIPCHK(c, hipMemsetAsync(P.fast_tile, 0xff, (size_t)p.total_tiles * 4, c->stream));
+    if (p.nblk > 0) HIPCHK(c, hipMemsetAsync(P.fast_tile, 0xff, (size_t)p.total_tiles * 4, c->stream));
     HIPCHK(c, hipMemsetAsync(P.tile_count, 0, 8, c->stream));
     HIPCHK(c, hipMemsetAsync(P.tncand, 0, (size_t)2 * p.total_tiles * 4, c->stream));
     HIPCHK(c, hipMemsetAsync(P.scan_all, 0, (size_t)2 * p.boxes.size() * 4, c->stream));
