@@ -47,7 +47,7 @@ METRIC = "MLUPS + IB nodes/s, % HBM roofline; FP16-storage & batched vs FP32 at 
 HBM_PEAK_GBS = 8000.0
 STORAGE = {"f64": 0, "f32": 1, "f16dev": 2, "bf16dev": 3}
 ELEM = {"f64": 8, "f32": 4, "f16dev": 2, "bf16dev": 2}
-BYTES_PER_NODE = 150.0  # per IB node and step: q, phi, weights, CSR, triangle records
+BYTES_PER_NODE = 150.0  # per IB node and step (estimate): q in and out, CSR, triangle ids, force, velocity
 BYTES_PER_BAND_CELL = 24.0  # per cell of a stamped tile: spread force read, velocity write
 TRACE = os.path.join(ROOT, "tests", "golden", "spreading_trace_oracle.json")
 PTRACE = os.path.join(ROOT, "tests", "golden", "precision_trace_oracle_tau{tau:g}.json")
